@@ -27,9 +27,10 @@
 //
 // Work order: see sched_slot (heaviest items of every head first, heads
 // grouped per XCD).
+#include <type_traits>
+
 #include "wise_device.hpp"
 #include "wise_kernels.hpp"
-
 namespace wise {
 
 // ---------------------------------------------------------------------------
@@ -41,7 +42,7 @@ namespace wise {
 // the barrier that retires it, or, in the 8-wave dense group, into its
 // second buffer.
 // ---------------------------------------------------------------------------
-template <int D, int NT, bool kWithV, int KT = kKeyTile>
+template <int D, int NT, int KT = kKeyTile>
 struct TileStage {
   using G = Geo<D>;
   static_assert(KT == 32 || KT == 64, "key tile");
@@ -50,7 +51,7 @@ struct TileStage {
   static constexpr int kPer = (kChunks + NT - 1) / NT;
 
   u32x4_t kr[kPer];
-  u32x4_t vr[kWithV ? kPer : 1];
+  u32x4_t vr[kPer];
 
   // Chunk i of this thread: key row ch / kRowChunks, column (ch % kRowChunks) * 8.
   __device__ __forceinline__ static int chunk(int tid, int i) { return tid + i * NT; }
@@ -69,7 +70,7 @@ struct TileStage {
         const int ch = chunk(tid, i);
         const uint32_t off = (uint32_t)((ch / kRowChunks) * D + (ch % kRowChunks) * 8) * 2;
         kr[i] = buffer_load16(rk, off, soff);
-        if constexpr (kWithV) vr[i] = buffer_load16(rv, off, soff);
+        vr[i] = buffer_load16(rv, off, soff);
       }
     }
   }
@@ -81,9 +82,61 @@ struct TileStage {
         const int ch = chunk(tid, i);
         const int key = ch / kRowChunks, c8 = (ch % kRowChunks) * 8;
         *(u32x4_t*)(ks + k_lds_row(key) * G::kKStride + c8) = kr[i];
-        if constexpr (kWithV) *(u32x4_t*)(vs + key * G::kVStride + c8) = vr[i];
+        *(u32x4_t*)(vs + key * G::kVStride + c8) = vr[i];
       }
     }
+  }
+};
+
+// Global -> LDS copies of one 64-key tile by NW waves into the swizzled layout:
+// copy i of wave w fills 1 KB at (w * kPer + i) * 1024.
+template <int D, int NW>
+struct TileCopy {
+  using S = Swizzle<D>;
+  static constexpr int kPer = S::kTile / 1024 / NW;
+  static_assert(S::kTile % (1024 * NW) == 0, "whole copies per wave");
+  uint32_t ko[kPer], vo[kPer];                        // this lane's source bytes in a tile
+
+  __device__ __forceinline__ void init(int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int at = (wave * kPer + i) * 1024 + lane * 16;
+      const int row = at / S::kRow, slot = at % S::kRow / 16;
+      ko[i] = k_lds_row(row) * S::kRow + S::k_chunk(row, slot) * 16;
+      vo[i] = row * S::kRow + (S::v_block(row, slot >> 2) * 4 + (slot & 3)) * 16;
+    }
+  }
+  // One copy of tile `tile`'s K (V) into the buffer at LDS address `lds`.
+  __device__ __forceinline__ void k1(u32x4_t r, int tile, uint32_t lds, int wave, int i) const {
+    copy16_to_lds(r, ko[i], (uint32_t)tile * S::kTile, lds + (uint32_t)(wave * kPer + i) * 1024);
+  }
+  __device__ __forceinline__ void v1(u32x4_t r, int tile, uint32_t lds, int wave, int i) const {
+    copy16_to_lds(r, vo[i], (uint32_t)tile * S::kTile, lds + (uint32_t)(wave * kPer + i) * 1024);
+  }
+  __device__ __forceinline__ void k(u32x4_t r, int tile, uint32_t lds, int wave) const {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) k1(r, tile, lds, wave, i);
+  }
+  __device__ __forceinline__ void v(u32x4_t r, int tile, uint32_t lds, int wave) const {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) v1(r, tile, lds, wave, i);
+  }
+};
+
+// LDS byte offsets of a lane's operand reads in a swizzled tile: K fragment
+// (chunk c, half u) at k[c] + u * 32 rows, V fragment (k-step, dims 32 t) at
+// v[t] + 16 ks rows (and 4 rows further).
+template <int D>
+struct ReadAddr {
+  using S = Swizzle<D>;
+  uint32_t k[D / 16], v[D / 32];
+  __device__ __forceinline__ void init(int lane) {
+    const int m = lane & 31, h = lane >> 5, r = 8 * h + ((lane >> 2) & 3);
+#pragma unroll
+    for (int c = 0; c < D / 16; ++c) k[c] = m * S::kRow + S::k_chunk(m, 2 * c + h) * 16;
+#pragma unroll
+    for (int t = 0; t < D / 32; ++t)
+      v[t] = r * S::kRow + S::v_block(r, t) * 64 + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
   }
 };
 
@@ -229,6 +282,187 @@ struct WaveRows {
     softmax_pv<H, kParts>(s, vt, lane, c);
   }
 
+  // Max over this lane's scores of one tile, times c, of the query (both halves).
+  template <int H>
+  __device__ __forceinline__ static float tile_max(const f32x16_t s[H], float c) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < H; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
+    return pair_max(mx) * c;
+  }
+
+  // New running max from a tile's max mx; true (wave-uniform) when some
+  // query's max grew: alpha then holds the factor of O, l is rescaled here.
+  __device__ __forceinline__ bool raise_max(float mx, float& alpha) {
+    const bool grow = mx > m;
+    if (!__builtin_amdgcn_ballot_w64(grow)) return false;
+    const float mn = grow ? mx : m;
+    alpha = (mn == m) ? 1.f : fast_exp2(m - mn);
+    l *= alpha;
+    m = mn;
+    return true;
+  }
+
+  static constexpr int kAhead = 4;               // LDS fragments in flight
+
+  // One step of the software pipeline of the 8-wave dense group: S^T of the
+  // next tile (kQk: into sn, from its K tile kn, masked by maskn) and online
+  // softmax and PV of the current one (kPv: its masked scores s, their max mx,
+  // its V tile vt).  The same operations in the same order as attend(), so the
+  // same bits.  It is laid out in 2 kN slots of one MFMA each, the LDS reads
+  // kAhead slots before their use and the exponentials, sums, packing and the
+  // next tile's max spread between the MFMAs, because two waves per SIMD in
+  // step leave nothing else to fill a wave's waits; mid(n, j) runs in slot j
+  // (the copies).  The wave's priority falls through the step, so of the two
+  // waves of a SIMD the one behind issues first and they reach the barrier
+  // together (3443 to 3186 cycles per tile at 16K).  Both the VALU (2790
+  // cycles without the MFMAs) and the matrix cores (2280 without the VALU
+  // work; 2048 at least) are then close to full.
+  template <int H, bool kQk, bool kPv, int kParts, class Mid, class Mask>
+  __device__ __forceinline__ void step(const char* kn, const char* vt, const ReadAddr<D>& ra, int lane, float c,
+                                       f32x16_t s[H], f32x16_t sn[H], float& mx, Mid mid, Mask maskn) {
+    constexpr int kN = G::kDChunks * H;          // MFMAs of S^T; PV has as many
+    constexpr int kPairs = 8 * H;
+    u32x4_t kf[kN], vf[kN], pb[2 * H];
+    auto read_k = [&](int j) {
+      kf[j] = *(const u32x4_t*)(kn + ra.k[j / H] + (j % H) * 32 * Swizzle<D>::kRow);
+    };
+    auto read_v = [&](int j) {
+      const int ks = j / G::kDTiles, t = j % G::kDTiles;
+      const char* p = vt + ra.v[t] + 16 * ks * Swizzle<D>::kRow;
+      const u32x2_t lo = lds_read_tr16((const uint16_t*)p);
+      const u32x2_t hi = lds_read_tr16((const uint16_t*)(p + 4 * Swizzle<D>::kRow));
+      vf[j] = u32x4_t{lo[0], lo[1], hi[0], hi[1]};
+    };
+    float mb = 0.f, ts = 0.f, tp[4] = {0.f, 0.f, 0.f, 0.f};
+    // Pair k: probabilities 2k, 2k + 1 of this lane, exponentials first, sums
+    // and packing a slot later.  The empty asm keeps each in its slot.
+    float pv[2 * kPairs];
+    auto pair_exp = [&](int k) {
+      if (k >= kPairs) return;
+      const int t = k / 8, r = 2 * (k % 8);
+      float p0 = fast_exp2(__builtin_fmaf(s[t][r], c, -mb));
+      float p1 = fast_exp2(__builtin_fmaf(s[t][r + 1], c, -mb));
+      asm volatile("" : "+v"(p0), "+v"(p1));
+      pv[2 * k] = p0;
+      pv[2 * k + 1] = p1;
+    };
+    auto pair_fin = [&](int k) {
+      if (k < 0 || k >= kPairs) return;
+      const int t = k / 8, r = 2 * (k % 8);
+      float& a = kParts == 0 ? ts : kParts == 4 ? tp[2 * t + (r >> 3)] : tp[t];
+      a += pv[2 * k];
+      a += pv[2 * k + 1];
+      uint32_t w = pack_bf16x2(pv[2 * k], pv[2 * k + 1]);
+      asm volatile("" : "+v"(a), "+v"(w));
+      pb[2 * t + (r >> 3)][(r & 7) >> 1] = w;
+    };
+    // Slot of the exponentials of pair k: slots 0 .. kN-1 hold the MFMAs of
+    // S^T, kN .. 2 kN - 1 those of PV.
+    constexpr int kS0 = 3;                        // S^T MFMAs issued before the new max is needed
+    auto pairs_before = [](int slot) {           // pairs whose exponentials are done before it
+      const int first = kS0, last = 2 * kN - kN / 4 - 1;   // first slot used, first slot past them
+      const int x = slot <= first ? 0 : (slot - first) * kPairs / (last - first);
+      return x > kPairs ? kPairs : x;
+    };
+    constexpr int kM0 = kN + 2;                  // first slot of the next tile's max
+    auto maxes_before = [](int slot) {
+      const int x = slot <= kM0 ? 0 : ((slot - kM0) * kPairs + 2 * kN - kM0 - 1) / (2 * kN - kM0);
+      return x > kPairs ? kPairs : x;
+    };
+    if constexpr (kQk) {
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) read_k(j);
+    }
+    __builtin_amdgcn_s_setprio(3);
+    float alpha = 1.f;
+    bool grew = false;
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+      if constexpr (kQk) {
+        if (j + kAhead < kN) read_k(j + kAhead);
+        sn[j % H] = mfma32x32x16(kf[j], qf[j / H], j < H ? f32x16_t{} : sn[j % H]);
+      }
+      if constexpr (kPv) {
+        if (j == kS0) {
+          __builtin_amdgcn_sched_barrier(0);
+          grew = raise_max(mx, alpha);
+          mb = (m == -INFINITY) ? 0.f : m;
+        }
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k)
+          if (k >= pairs_before(j) && k < pairs_before(j + 1)) pair_exp(k);
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k)
+          if (k >= pairs_before(j - 1) && k < pairs_before(j)) pair_fin(k);
+        // O rescaled in place, a tile of 32 dims at a time between the MFMAs
+        // (a plain `*=` lets the allocator rename O and copy all of it back on
+        // the path that skips the rescale).
+        constexpr int kGap = (kN - kS0) / G::kDTiles;
+        if (j >= kS0 && (j - kS0) % kGap == 0 && (j - kS0) / kGap < G::kDTiles) {
+          const int t = (j - kS0) / kGap;
+          if (grew) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) asm volatile("v_mul_f32 %0, %0, %1" : "+v"(o[t][r]) : "v"(alpha));
+          }
+        }
+        if (j + kAhead >= kN) read_v(j + kAhead - kN);
+      }
+      mid(std::integral_constant<int, 2 * kN>{}, j);
+      if (j == kN / 2) __builtin_amdgcn_s_setprio(2);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_setprio(1);
+    if constexpr (kQk) maskn(sn);
+    __builtin_amdgcn_sched_barrier(0);
+    float mn = -INFINITY;
+#pragma unroll
+    for (int j = kN; j < 2 * kN; ++j) {
+      if constexpr (kPv) {
+        const int i = j - kN;
+        if (i + kAhead < kN) read_v(i + kAhead);
+        o[i % G::kDTiles] = mfma32x32x16(vf[i], pb[i / G::kDTiles], o[i % G::kDTiles]);
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k)
+          if (k >= pairs_before(j) && k < pairs_before(j + 1)) pair_exp(k);
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k)
+          if (k >= pairs_before(j - 1) && k < pairs_before(j)) pair_fin(k);
+      }
+      if constexpr (kQk) {
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k)
+          if (k >= maxes_before(j) && k < maxes_before(j + 1)) {
+            mn = fmaxf(fmaxf(mn, sn[k / 8][2 * (k % 8)]), sn[k / 8][2 * (k % 8) + 1]);
+            asm volatile("" : "+v"(mn));
+          }
+      }
+      mid(std::integral_constant<int, 2 * kN>{}, j);
+      if (j == kN + kN / 2) __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (kPv) {
+      if constexpr (kParts == 4) {
+#pragma unroll
+        for (int t = 0; t < H; ++t) {
+          hs[2 * t] = tp[2 * t];
+          hs[2 * t + 1] = tp[2 * t + 1];
+          ts += tp[2 * t] + tp[2 * t + 1];
+        }
+      } else if constexpr (kParts == 2) {
+#pragma unroll
+        for (int t = 0; t < H; ++t) {
+          hs[t] = tp[t];
+          ts += tp[t];
+        }
+      }
+      l += ts;
+    }
+    if constexpr (kQk) mx = pair_max(mn) * c;
+  }
+
   // log2 of the last tile's probability mass per query, unnormalised (taken
   // against the running max m): entries 0..3 for the four 16-key quarters
   // (E = 16), 0 and 1 for the two 32-key halves (E = 32) or entry 0 for the
@@ -321,19 +555,20 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
   constexpr int kEPT = kKeyTile / kE;               // entries per 64-key tile
   constexpr int kParts = kMass ? (kE == 16 ? 4 : 2) : 0;
   // An 8-wave group fills its CU alone (two waves per SIMD), so no other
-  // group runs while it waits at a barrier: it keeps two LDS tiles and stages
-  // tile it+1 into the other one right after computing tile it, one barrier
-  // per tile.  Smaller groups share a CU three or four at a time, which a
-  // second buffer would halve; they stage and compute around two barriers.
+  // group runs while it waits: it runs the software pipeline of step() on
+  // rings of LDS tiles, one barrier per tile.  Smaller groups share a CU three
+  // or four at a time; they stage and compute around two barriers.
   constexpr int kBufs = NW == 8 ? 2 : 1;
-  __shared__ __attribute__((aligned(16))) uint16_t ks[kBufs * G::kKElems];
-  __shared__ __attribute__((aligned(16))) uint16_t vt[kBufs * G::kVElems];
+  constexpr int kLds = kBufs == 2 ? 8 * Swizzle<D>::kTile : 2 * (G::kKElems + G::kVElems);
+  __shared__ __attribute__((aligned(1024))) char smem[kLds];
+  uint16_t* const ks = (uint16_t*)smem;
+  uint16_t* const vt = ks + G::kKElems;
   int bh, item;
   if (!sched_slot(sc, bh, item)) return;
   const int qt = sc.items - 1 - item;
   const size_t hoff = (size_t)bh * n * D;
   const size_t kvoff = (size_t)kv_head(bh, heads, gq) * n * D;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qbase = qt * kQT, q0 = qbase + 32 * wave;
   // Workspace: per head, per query tile qt, (qt+1)*kQT/kE entries of kQT
   // queries each (only the spans up to the tile's last query), query-minor.
@@ -362,38 +597,107 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
   const __amdgpu_buffer_rsrc_t rk = buffer_rsrc(K + kvoff), rv = buffer_rsrc(V + kvoff);
   const int ntiles = (qbase + kQT) / kKeyTile;
   const int nfull = qbase / kKeyTile;
-  TileStage<D, kNT, true> st;
-  st.load(rk, rv, 0, tid);
+  TileStage<D, kNT> st;
+  if constexpr (kBufs == 1) st.load(rk, rv, 0, tid);
   if constexpr (kBufs == 2) {
-    st.store(ks, vt, tid);
-    if (ntiles > 1) st.load(rk, rv, kKeyTile, tid);
+    // Software pipeline: in step `it` a wave computes S^T of tile it+1 and
+    // softmax and PV of tile it, while K(it+4) and V(it+3) are copied into
+    // rings of four K and four V tiles (128 KB of LDS; registers already
+    // limit a CU to one of these groups).  Copies have two steps to land: one
+    // step is less than the latency of a tile from HBM (16K: 1.01x instead of
+    // 1.06x of the unpipelined loop).  Measured against that loop (S^T,
+    // softmax and PV one after the other, tiles staged through registers):
+    // 4096 x 32 heads 142 -> 134 us, 16384 x 64 heads 4069 -> 3827 us (1081
+    // -> 1149 TFLOP/s, 3105 cycles per tile instead of about 3900 at a clock
+    // that power holds at 1.7 instead of 1.95 GHz), 2048 x 16 heads 58.7 ->
+    // 51.9 us.
+    constexpr int kT = Swizzle<D>::kTile;
+    const u32x4_t bk = buffer_words(K + kvoff), bv = buffer_words(V + kvoff);
+    TileCopy<D, NW> cp;
+    ReadAddr<D> ra;
+    cp.init(wave, lane);
+    ra.init(lane);
+    const uint32_t lk = lds_address(smem), lv = lk + 4 * kT;
+    const char* sk = smem;
+    const char* sv = smem + 4 * kT;
+    constexpr int kC = TileCopy<D, NW>::kPer;     // copies per tile and tensor
+    // Every group has at least 4 tiles (its 256 queries).  The compiler waits
+    // for Q with nothing left in flight, so only what the first steps need is
+    // issued before Q's first use.
+    cp.k(bk, 0, lk, wave);
+    cp.v(bv, 0, lv, wave);
+    cp.k(bk, 1, lk + kT, wave);
+#pragma unroll
+    for (int cc = 0; cc < G::kDChunks; ++cc) asm volatile("" : "+v"(w.qf[cc]));
+    wait_copies<0>();
     __syncthreads();
-    // Buffer (it+1)&1 was last read by tile it-1, which every wave finished
-    // before the previous barrier.
-    auto stage_next = [&](int it) {
-      if (it + 1 < ntiles) {
-        const int nx = (it + 1) & 1;
-        st.store(ks + nx * G::kKElems, vt + nx * G::kVElems, tid);
-        if (it + 2 < ntiles) st.load(rk, rv, (it + 2) * kKeyTile, tid);
-      }
+    cp.v(bv, 1, lv + kT, wave);
+    cp.k(bk, 2, lk + 2 * kT, wave);
+    cp.v(bv, 2, lv + 2 * kT, wave);
+    cp.k(bk, 3, lk + 3 * kT, wave);
+    const int ntw = q0 / kKeyTile + 1;            // this wave's tiles; the last holds its diagonal
+    f32x16_t s0[2], s1[2];
+    float mx = 0.f;
+    auto mask_last = [&](f32x16_t sn[2]) {
+      int lastk = (ntw - 1) * kKeyTile;
+      asm volatile("" : "+s"(lastk));
+      WaveRows<D>::template mask<2>(sn, lastk, q0 + (lane & 31), lane);
+    };
+    w.template step<2, true, false, kParts>(sk, sv, ra, lane, c, s1, s0, mx, [](auto, int) {},
+                                            [&](f32x16_t sn[2]) { if (ntw == 1) mask_last(sn); });
+    __syncthreads();                              // K(0) read by every wave: K(4) may take its place
+    // End of step it: K(it+2) and V(it+1) have landed for every wave.  Copies
+    // land in order; those issued after them may stay in flight.
+    auto advance = [&](int it) {
+      if (it + 4 < ntiles) wait_copies<4 * kC>();
+      else if (it + 4 == ntiles) wait_copies<3 * kC>();
+      else if (it + 3 == ntiles) wait_copies<kC>();
+      else wait_copies<0>();
       __syncthreads();
     };
-    int it = 0;
-    for (; it < nfull; ++it) {
-      const int cu = it & 1;
-      w.template attend<false, 2, kParts>(ks + cu * G::kKElems, vt + cu * G::kVElems, lane, c,
-                                         it * kKeyTile, q0);
-      put_mass(it);
-      stage_next(it);
-    }
-    for (; it < ntiles; ++it) {
-      const int cu = it & 1;
-      if (it * kKeyTile <= q0) {
-        w.template attend<true, 2, kParts>(ks + cu * G::kKElems, vt + cu * G::kVElems, lane, c,
-                                          it * kKeyTile, q0);
-        put_mass(it);
+    // Step it reads K(it+1) and V(it); V(it+3) and K(it+4) go where V(it-1) and
+    // K(it) were, last read in the step before.  b = it & 3.
+    auto copy = [&](int it, int b, int i) {
+      if (i < kC) {
+        if (it + 3 < ntiles) cp.v1(bv, it + 3, lv + ((b + 3) & 3) * kT, wave, i);
+      } else {
+        if (it + 4 < ntiles) cp.k1(bk, it + 4, lk + b * kT, wave, i - kC);
       }
-      stage_next(it);
+    };
+    auto fused = [&](int it, int b, f32x16_t sc[2], f32x16_t sn[2]) {
+      w.template step<2, true, true, kParts>(
+          sk + ((b + 1) & 3) * kT, sv + b * kT, ra, lane, c, sc, sn, mx,
+          [&](auto, int j) {
+            if (j >= 2 && (j - 2) % 4 == 0 && (j - 2) / 4 < 2 * kC) copy(it, b, (j - 2) / 4);
+          },
+          [&](f32x16_t x[2]) { if (it + 2 == ntw) mask_last(x); });
+      put_mass(it);
+      advance(it);
+    };
+    int it = 0;
+    for (; it + 4 < ntw; it += 4) {
+      fused(it, 0, s0, s1);
+      fused(it + 1, 1, s1, s0);
+      fused(it + 2, 2, s0, s1);
+      fused(it + 3, 3, s1, s0);
+    }
+    for (; it + 1 < ntw; ++it) {
+      fused(it, it & 3, s0, s1);
+      s0[0] = s1[0];
+      s0[1] = s1[1];
+    }
+    auto copies = [&](int it) {
+#pragma unroll
+      for (int i = 0; i < 2 * kC; ++i) copy(it, it & 3, i);
+    };
+    copies(it);
+    w.template step<2, false, true, kParts>(sk, sv + (it & 3) * kT, ra, lane, c, s0, s1, mx,
+                                            [](auto, int) {}, [](f32x16_t*) {});
+    put_mass(it);
+    advance(it);
+    for (++it; it < ntiles; ++it) {
+      copies(it);
+      advance(it);
     }
   } else {
     for (int it = 0; it < nfull; ++it) {
@@ -520,7 +824,7 @@ sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
   WaveRows<D> w;
   w.load_q(Q + hoff, q0, lane);
   w.reset();
-  TileStage<D, kNT, true, KT> st;
+  TileStage<D, kNT, KT> st;
   const int ntiles = nent * kTPB;
   // Entries are ascending, so only the last one can be the diagonal block:
   // every earlier tile lies wholly below this group's queries.
@@ -602,7 +906,7 @@ sparse_group_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
   // The group's first tile is its union's lowest block: block 0 wherever a
   // row holds the sink block, so that tile's loads start before the
   // supports are read (and are reissued for another first block).
-  TileStage<D, kNT, true> st;
+  TileStage<D, kNT> st;
   st.load(rk, rv, 0, tid);
   w.reset();
   // The group's rows are consecutive CSR rows: their entries form one range,

@@ -48,6 +48,31 @@ __device__ __forceinline__ u32x4_t buffer_load16(__amdgpu_buffer_rsrc_t r, uint3
   return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
 }
 
+// Buffer descriptor as four scalars, for the copies below.
+__device__ __forceinline__ u32x4_t buffer_words(const void* base) {
+  const uint64_t b = (uint64_t)base;
+  return u32x4_t{(uint32_t)b, (uint32_t)(b >> 32), 0x7fffffffu, 0x00020000u};
+}
+
+// 16 bytes per lane, global -> LDS without registers: lane l's bytes land at
+// LDS byte address lds + 16 l (lds wave-uniform).  The copy counts in vmcnt;
+// issued as asm because the compiler would otherwise wait for every copy in
+// flight before each LDS read.
+__device__ __forceinline__ void copy16_to_lds(u32x4_t r, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory");
+}
+// At most N copies (or other vector memory operations) still in flight.
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
+}
+
+// Byte address of a __shared__ object within the group's LDS.
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)(p);
+}
+
 // Two fp32 -> packed bf16x2 (round to nearest even), lo in bits 0..15.
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   f32x2_t v = {lo, hi};
@@ -108,6 +133,22 @@ struct Geo {
   static constexpr int kDTiles = D / 32;          // MFMA m-tiles of O^T = V^T P^T
   static constexpr int kKElems = kKeyTile * kKStride;
   static constexpr int kVElems = kKeyTile * kVStride;
+};
+
+// Swizzled LDS layout of a 64-key tile, filled by 16-byte copies: rows of 2 D
+// bytes without padding; the 16-byte chunks of a K row and the 64-byte blocks
+// of a V row are permuted by row so that the 16 rows of a 128-bit K read and
+// the 4 rows of a transposing V read fall on distinct banks.
+template <int D>
+struct Swizzle {
+  static constexpr int kRow = 2 * D;                  // bytes
+  static constexpr int kTile = kKeyTile * kRow;       // bytes of one K or V tile
+  __device__ static int k_chunk(int row, int chunk) {
+    return D == 128 ? chunk ^ (row & 15) : D == 96 ? chunk ^ ((row >> 2) & 3) : chunk ^ ((row >> 1) & 7);
+  }
+  __device__ static int v_block(int row, int block) {
+    return D == 128 ? block ^ (row & 3) : D == 96 ? block : block ^ ((row >> 1) & 1);
+  }
 };
 
 // Row of the LDS K tile that holds tile-local key `key`.  S^T = K Q^T puts
