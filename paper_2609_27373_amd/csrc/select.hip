@@ -6,22 +6,18 @@
 // reaches tau * total.  The schedule is a device-resident CSR (Appendix B,
 // "Sparse-kernel implementation") plus a longest-support-first row order.
 //
-//   select_rows_kernel   one wave per row: rank every candidate by
-//                        (mass desc, block asc), sum the ordered masses
-//                        sequentially in fp64 (the same association as a
-//                        left-to-right prefix sum), cut, add forced blocks,
-//                        emit a bitmask and a count
-//   scan_kernel          exclusive scan of counts -> row_ptr
-//   scatter_kernel       bitmask -> ascending col_idx
-//   order_kernel         per (batch, head): its rows by count descending
-//                        (ties by row id), heads in ascending order
+//   select_rows_kernel   one wave per row: the cut of the masses ordered by
+//                        (mass desc, block asc) and summed in that order in
+//                        fp64, forced blocks added, a bitmask and a count
+//   csr_kernel           counts -> row_ptr (exclusive scan), bitmask ->
+//                        ascending col_idx, and per (batch, head) its rows by
+//                        count descending (ties by row id)
 //
 // The paper's own working set (Section 5.1, eq. block_working_set) is the
 // union over the discovery window of per-step sets B_q^(t, eta).  For it the
 // per-row kernel runs on one step's masses with no forced blocks and leaves
 // the step's bitmask with the caller; union_rows_kernel ORs any number of
-// such masks, adds the forced blocks, and feeds the same scan / scatter /
-// order kernels.  Two diagnostics close the file: the (intersection, union)
+// such masks, adds the forced blocks, and feeds the same csr kernel.  Two diagnostics close the file: the (intersection, union)
 // sizes of two masks (the adjacent rolling-set Jaccard of Appendix C,
 // "Stability of the Deployed Working Set") and the attention mass a support
 // retains from one step's block masses (Section 7.1 and Appendix B, the
@@ -35,7 +31,6 @@
 namespace wise {
 
 constexpr int kSelWaves = 4;        // rows per work-group in the per-row kernels
-constexpr int kOrderThreads = 256;
 
 // Orderable 32-bit image of a float: unsigned order == float order.
 __device__ __forceinline__ uint32_t float_key(float x) {
@@ -43,40 +38,67 @@ __device__ __forceinline__ uint32_t float_key(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// E = candidates per lane (ceil(nb / 64) rounded up to a power of two).
-template <int E>
-__global__ void __launch_bounds__(kSelWaves * 64)
-select_rows_kernel(const float* __restrict__ acc, int rows, int nb, double tau, uint32_t flags,
-                   int32_t* __restrict__ counts, uint64_t* __restrict__ masks, int words) {
-  extern __shared__ __attribute__((aligned(16))) uint64_t sel_smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row = blockIdx.x * kSelWaves + wave;
-  const bool active = row < rows;
-  uint64_t* keys = sel_smem + (size_t)wave * 2 * nb;   // [nb] sort keys, later prefixes
-  double* sv = (double*)(keys + nb);                    // [nb] masses in sorted order
-  const int qb = active ? row % nb : 0;
-  const int cnt = active ? qb + 1 : 0;
-  const float* v = acc + (size_t)(active ? row : 0) * nb;
+// Order LDS traffic within one wave (each wave of the per-row kernel works on
+// its own row and its own LDS, so the group needs no barrier).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
-  // 1. composite keys: mass descending, then block index ascending
-  float x[E];
+// Lane l's x from another lane by DPP, 0 where the pattern gives none.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, kCtrl, kRows, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kCtrl, kRows, 0xF, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// Inclusive sums over the wave's lanes, on the VALU (a shuffle per step goes
+// through LDS): shifts within rows of 16, then the row ends broadcast.
+__device__ __forceinline__ double wave_scan(double x) {
+  x += dpp_f64<0x111, 0xF>(x);   // row_shr 1
+  x += dpp_f64<0x112, 0xF>(x);
+  x += dpp_f64<0x114, 0xF>(x);
+  x += dpp_f64<0x118, 0xF>(x);
+  x += dpp_f64<0x142, 0xA>(x);   // row_bcast 15 into rows 1 and 3
+  x += dpp_f64<0x143, 0xC>(x);   // row_bcast 31 into rows 2 and 3
+  return x;
+}
+__device__ __forceinline__ double read_lane(double x, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum(double x) { return read_lane(wave_scan(x), 63); }
+
+// LDS bytes of one row's wave: 256 digit sums, or nb keys and nb sorted masses.
+constexpr int kDigitBins = 256;
+__host__ __device__ constexpr size_t select_row_lds(int nb) {
+  return (size_t)(2 * nb > kDigitBins ? 2 * nb : kDigitBins) * 8;
+}
+
+// k* of one row by definition: rank every candidate, add the ordered masses
+// one by one in fp64.  keys[e] / rank[e]: candidate lane + 64 e.
+template <int E>
+__device__ int cut_by_rank(const float x[E], int cnt, double tau, uint64_t* lds, int nb, int lane,
+                           int rank[E]) {
+  uint64_t* keys = lds;                                 // [nb] sort keys, later prefixes
+  double* sv = (double*)(lds + nb);                     // [nb] masses in sorted order
   uint64_t key[E];
+  // composite keys: mass descending, then block index ascending
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int b = lane + 64 * e;
-    x[e] = 0.f;
     key[e] = 0;
+    rank[e] = 0;
     if (b < cnt) {
-      x[e] = v[b];
       key[e] = ((uint64_t)float_key(x[e]) << 32) | (uint32_t)(~(uint32_t)b);
       keys[b] = key[e];
     }
   }
-  __syncthreads();
-  // 2. rank = number of candidates ordered before this one
-  int rank[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) rank[e] = 0;
+  wave_sync();
+  // rank = number of candidates ordered before this one
   for (int c = 0; c < cnt; ++c) {
     const uint64_t kc = keys[c];
 #pragma unroll
@@ -85,16 +107,16 @@ select_rows_kernel(const float* __restrict__ acc, int rows, int nb, double tau, 
 #pragma unroll
   for (int e = 0; e < E; ++e)
     if (lane + 64 * e < cnt) sv[rank[e]] = (double)x[e];
-  __syncthreads();
-  // 3. sequential fp64 prefix sums in sorted order (identical in every lane)
+  wave_sync();
+  // sequential fp64 prefix sums in sorted order (identical in every lane)
   double* pre = (double*)keys;
   double run = 0.0;
   for (int r = 0; r < cnt; ++r) {
     run += sv[r];
     if (lane == 0) pre[r] = run;
   }
-  __syncthreads();
-  // 4. k* = min{k >= 0 : c_k >= tau * total}, c_0 = 0
+  wave_sync();
+  // k* = min{k >= 0 : c_k >= tau * total}, c_0 = 0
   const double thr = tau * run;
   int kstar = cnt;
   if (thr <= 0.0) {
@@ -105,23 +127,188 @@ select_rows_kernel(const float* __restrict__ acc, int rows, int nb, double tau, 
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) kstar = min(kstar, __shfl_xor(kstar, off, 64));
   }
-  // 5. selection bitmask, forced blocks, empty -> diagonal
+  wave_sync();
+  return kstar;
+}
+
+// The same cut without sorting, for the masses attention gives.  fp64 sums of
+// fp32 masses are exact, whatever their order, while every mass is a multiple
+// of 2^-53 times a power of two above their sum: so for the heavy masses
+// (exponent at most 28 below the total's) the ordered prefix sums are plain
+// sums, and the cut is found digit by digit of the mass bits from sums per digit.  The light
+// masses only follow the heavy ones in the order; where there are at most 64
+// they are ranked and added one by one to give the total.  Returns false
+// (nothing decided) for negative, infinite or NaN masses, more light ones, or
+// a cut among them: cut_by_rank then does the row.  On success sel[e] tells
+// whether candidate lane + 64 e is among the first k*.
+// Bound by instruction issue: about four passes of E LDS adds and one 64-lane
+// scan, where ranking takes nb / 2 comparisons per candidate and a serial sum.
+// Whole selection, both ways: 28160 rows of 128 blocks 108.3 -> 30.0 us (of
+// which this kernel about 24), 8192 rows of 128 41.6 -> 19.1 us, 8192 rows of
+// 1024 blocks 615 -> 88.6 us (cut_by_rank on every row, before the CSR's
+// change too).
+template <int E>
+__device__ bool cut_by_digits(const float x[E], int cnt, double tau, uint64_t* lds, int lane,
+                              bool sel[E]) {
+  uint32_t u[E];
+  bool plain = true;
+  double part = 0.0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    u[e] = lane + 64 * e < cnt ? __builtin_bit_cast(uint32_t, x[e]) : 0u;
+    plain = plain && u[e] < 0x7f800000u;
+    part += (double)__builtin_bit_cast(float, u[e]);
+    sel[e] = false;
+  }
+  if (__builtin_amdgcn_ballot_w64(!plain)) return false;
+  const double about = wave_sum(part);                  // the total but for its rounding
+  if (about == 0.0) return true;                        // k* = 0
+  // about < 2^(et + 1): masses with biased exponent >= et - 29 + 127 are heavy.
+  const int et = (int)((__builtin_bit_cast(uint64_t, about) >> 52) & 0x7ff) - 1023;
+  const int e0 = max(et + 127 - 28, 0);
+  const uint32_t heavy = (uint32_t)e0 << 23;            // smallest heavy mass bits
+  double hp = 0.0;
+  int light = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    if (u[e] >= heavy) hp += (double)__builtin_bit_cast(float, u[e]);
+    light += __builtin_popcountll(__builtin_amdgcn_ballot_w64(u[e] > 0 && u[e] < heavy));
+  }
+  const double big = wave_sum(hp);
+  double total = big;
+  if (light > 64) return false;
+  if (light > 0) {
+    uint32_t* lu = (uint32_t*)lds;
+    int at = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const bool l = u[e] > 0 && u[e] < heavy;
+      const uint64_t b = __builtin_amdgcn_ballot_w64(l);
+      if (l) lu[at + __builtin_popcountll(b & ((1ull << lane) - 1ull))] = u[e];
+      at += __builtin_popcountll(b);
+    }
+    wave_sync();
+    const uint32_t mine = lane < light ? lu[lane] : 0u;
+    int rank = 0;
+    for (int c = 0; c < light; ++c) {
+      const uint32_t o = lu[c];
+      rank += (o > mine || (o == mine && c < lane)) ? 1 : 0;
+    }
+    wave_sync();
+    if (lane < light) lu[rank] = mine;
+    wave_sync();
+    for (int r = 0; r < light; ++r) total += (double)__builtin_bit_cast(float, lu[r]);
+    wave_sync();
+  }
+  const double thr = tau * total;
+  if (thr > big) return false;
+  double* bins = (double*)lds;
+  uint32_t head = 0;                                    // leading bits of the cut's mass
+  double above = 0.0;                                   // sum of all masses with larger leading bits
+  uint32_t cut = 0;
+  bool found = false;
+#pragma unroll
+  for (int pass = 0; pass < 4 && !found; ++pass) {
+    constexpr int kShift[4] = {23, 15, 7, 0};
+    const int shift = kShift[pass], width = pass < 3 ? 8 : 7;
+    const uint32_t mask = (1u << width) - 1u;
+    double2* own4 = (double2*)bins + 2 * (63 - lane);     // digits 252 - 4 l .. 255 - 4 l
+    own4[0] = own4[1] = double2{0.0, 0.0};
+    wave_sync();
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (u[e] >= heavy && u[e] > 0 && (u[e] >> shift >> width) == head)
+        __hip_atomic_fetch_add(&bins[(u[e] >> shift) & mask], (double)__builtin_bit_cast(float, u[e]),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    wave_sync();
+    // lane l holds the four digits 255 - 4 l downwards
+    const double2 low2 = own4[0], high2 = own4[1];
+    wave_sync();
+    const double d[4] = {high2.y, high2.x, low2.y, low2.x};
+    const double own = d[0] + d[1] + d[2] + d[3];
+    const double c = wave_scan(own);
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(above + c >= thr);
+    const int first = __builtin_ctzll(hit);             // thr <= big: some lane reaches it
+    double before = above + (c - own);
+    int digit = 0;
+    bool done = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (!done && before + d[i] >= thr) {
+        digit = kDigitBins - 1 - 4 * lane - i;
+        done = true;
+      }
+      if (!done) before += d[i];
+    }
+    digit = __builtin_amdgcn_readlane(digit, first);
+    above = read_lane(before, first);
+    head = (head << width) | (uint32_t)digit;
+    int members = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const uint64_t b = __builtin_amdgcn_ballot_w64(u[e] > 0 && (u[e] >> shift) == head);
+      members += __builtin_popcountll(b);
+      if (b) cut = __builtin_amdgcn_readlane(u[e], __builtin_ctzll(b));
+    }
+    found = members == 1 || pass == 3;                  // all members equal `cut`
+  }
+  // Everything heavier, and of the masses equal to the cut as many, lowest
+  // blocks first, as reach the threshold.
+  const double val = (double)__builtin_bit_cast(float, cut);
+  int need = 0;
+  for (double c = above; c < thr; c += val) ++need;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint64_t b = __builtin_amdgcn_ballot_w64(u[e] == cut);
+    const int ahead = __builtin_popcountll(b & ((1ull << lane) - 1ull));
+    sel[e] = u[e] > cut || (u[e] == cut && ahead < need);
+    need -= min(need, __builtin_popcountll(b));
+  }
+  return true;
+}
+
+// E = candidates per lane (ceil(nb / 64) rounded up to a power of two).  One
+// wave per row, four rows per group, no barriers.
+template <int E>
+__global__ void __launch_bounds__(kSelWaves * 64)
+select_rows_kernel(const float* __restrict__ acc, int rows, int nb, double tau, uint32_t flags,
+                   int32_t* __restrict__ counts, uint64_t* __restrict__ masks, int words) {
+  extern __shared__ __attribute__((aligned(16))) uint64_t sel_smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row = blockIdx.x * kSelWaves + wave;
+  if (row >= rows) return;
+  uint64_t* lds = sel_smem + (size_t)wave * (select_row_lds(nb) / 8);
+  const int qb = row % nb;
+  const int cnt = qb + 1;
+  const float* v = acc + (size_t)row * nb;
+  float x[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) x[e] = lane + 64 * e < cnt ? v[lane + 64 * e] : 0.f;
+  bool sel[E];
+  if (!cut_by_digits<E>(x, cnt, tau, lds, lane, sel)) {
+    int rank[E];
+    const int kstar = cut_by_rank<E>(x, cnt, tau, lds, nb, lane, rank);
+#pragma unroll
+    for (int e = 0; e < E; ++e) sel[e] = rank[e] < kstar;
+  }
+  // selection bitmask, forced blocks, empty -> diagonal
   int total = 0;
   uint64_t mword[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int b = lane + 64 * e;
     bool s = false;
-    if (b < cnt)
-      s = rank[e] < kstar || (b == 0 && (flags & 1u)) || (b == qb && (flags & 2u));
+    if (b < cnt) s = sel[e] || (b == 0 && (flags & 1u)) || (b == qb && (flags & 2u));
     mword[e] = __builtin_amdgcn_ballot_w64(s);
     total += __builtin_popcountll(mword[e]);
   }
   if (total == 0) {
-    mword[qb >> 6] |= 1ull << (qb & 63);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (e == qb >> 6) mword[e] |= 1ull << (qb & 63);
     total = 1;
   }
-  if (active && lane == 0) {
+  if (lane == 0) {
     if (counts != nullptr) counts[row] = total;
 #pragma unroll
     for (int e = 0; e < E; ++e)
@@ -154,7 +341,8 @@ __device__ __forceinline__ int block_scan_1024(int x, int* wsum) {
   return x + add;
 }
 
-// row_ptr[0] = 0, row_ptr[r+1] = counts[0] + ... + counts[r].
+// row_ptr[0] = 0, row_ptr[r+1] = counts[0] + ... + counts[r], by one group.
+// Only for row counts past kSumRows (see launch_csr).
 __global__ void __launch_bounds__(1024)
 scan_kernel(const int32_t* __restrict__ counts, int rows, int32_t* __restrict__ row_ptr) {
   __shared__ int wsum[16];
@@ -176,38 +364,113 @@ scan_kernel(const int32_t* __restrict__ counts, int rows, int32_t* __restrict__ 
   }
 }
 
-// col_idx[row_ptr[r] ..] = set bits of the row's mask, ascending.
-__global__ void __launch_bounds__(kSelWaves * 64)
-scatter_kernel(const uint64_t* __restrict__ masks, const int32_t* __restrict__ row_ptr, int rows,
-               int words, int32_t* __restrict__ col_idx) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * kSelWaves + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  int pos = row_ptr[row];
-  const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int e = 0; e < words; ++e) {
-    const uint64_t m = masks[(size_t)row * words + e];
-    if ((m >> lane) & 1ull) col_idx[pos + __builtin_popcountll(m & below)] = 64 * e + lane;
-    pos += __builtin_popcountll(m);
-  }
-}
+// Counts and bitmasks -> row_ptr, col_idx and row order.  One group takes
+// kCsrRows rows of one head (grid: heads x chunks of a head):
+//   its first entry   the sum of every earlier row's count (read again by each
+//                     group: at most kSumRows counts from L2), or row_ptr
+//                     where the scan has run
+//   row_ptr           the scan of its own rows' counts from there
+//   col_idx           one wave per row at a time: set bits of the mask, ascending
+//   order             row r of a head lands at rank(r) = #{rows with a larger
+//                     count} + #{earlier rows with the same count}, eight
+//                     lanes per row over the head's counts in LDS
+// Latency bound (6 us for 28160 rows, where a one-group scan, a scatter and an
+// order kernel took about 45); 16 waves per group put eight rows' masks of
+// each wave in flight at once.
+constexpr int kCsrRows = 128;
 
-// Row order: one work-group per (batch, head).  Row r of the head lands at
-// rank(r) = #{rows with a larger count} + #{earlier rows with the same count}.
-__global__ void __launch_bounds__(kOrderThreads)
-order_kernel(const int32_t* __restrict__ counts, int nb, int32_t* __restrict__ order) {
-  extern __shared__ int32_t o_smem[];
-  const int base = blockIdx.x * nb;
-  for (int r = threadIdx.x; r < nb; r += kOrderThreads) o_smem[r] = counts[base + r];
-  __syncthreads();
-  for (int r = threadIdx.x; r < nb; r += kOrderThreads) {
-    const int c = o_smem[r];
-    int rank = 0;
-    for (int t = 0; t < nb; ++t) {
-      const int ct = o_smem[t];
-      rank += (ct > c || (ct == c && t < r)) ? 1 : 0;
+template <bool kScanned>
+__global__ void __launch_bounds__(1024)
+csr_kernel(const int32_t* __restrict__ counts, const uint64_t* __restrict__ masks, int nb, int words,
+           int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx, int32_t* __restrict__ order) {
+  __shared__ int head[1024];             // nb <= kMaxSelectBlocks
+  __shared__ int start[kCsrRows];
+  __shared__ int wsum[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int base = blockIdx.x * nb;                        // the head's first row
+  const int r0 = blockIdx.y * kCsrRows, nr = min(kCsrRows, nb - r0);
+  const int first = base + r0;
+  // Up to eight rows' masks per wave, loaded before the sums they wait for.
+  constexpr int kRowsPerWave = kCsrRows / 16;
+  uint64_t m[kRowsPerWave];
+#pragma unroll
+  for (int i = 0; i < kRowsPerWave; ++i) {
+    const int r = wave + 16 * i;
+    m[i] = r < nr && lane < words ? masks[(size_t)(first + r) * words + lane] : 0ull;
+  }
+  if (tid < nb) head[tid] = counts[base + tid];
+  int before = 0;
+  if constexpr (!kScanned) {
+    const int4* c4 = (const int4*)counts;                  // 256-byte aligned
+    const int n4 = first >> 2;
+    int sum = 0;
+#pragma unroll 4
+    for (int i = tid; i < n4; i += 1024) {
+      const int4 c = c4[i];
+      sum += c.x + c.y + c.z + c.w;
     }
-    order[base + rank] = base + r;
+    if (tid < (first & 3)) sum += counts[4 * n4 + tid];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    if (lane == 0) wsum[wave] = sum;
+  }
+  __syncthreads();
+  if constexpr (kScanned) {
+    before = row_ptr[first];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) before += wsum[i];
+  }
+  // Exclusive scan of the chunk's counts: two waves, the second adds the
+  // first's total.
+  if (tid < kCsrRows) {
+    const int x = tid < nr ? head[r0 + tid] : 0;
+    int inc = x;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int y = __shfl_up(inc, off, 64);
+      if (lane >= off) inc += y;
+    }
+    if (wave == 1) {
+      int low = head[r0 + lane];                           // rows 0 .. 63 of the chunk: nr > 64 or unused
+      if (r0 + lane >= nb) low = 0;
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) low += __shfl_xor(low, off, 64);
+      inc += low;
+    }
+    if (tid < nr) {
+      start[tid] = before + inc - x;
+      if constexpr (!kScanned) row_ptr[first + tid + 1] = before + inc;
+    }
+  }
+  if (!kScanned && first == 0 && tid == 0) row_ptr[0] = 0;
+  __syncthreads();
+  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int i = 0; i < kRowsPerWave; ++i) {
+    const int r = wave + 16 * i;
+    if (r >= nr) break;
+    int pos = start[r];
+    for (int e = 0; e < words; ++e) {
+      const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)m[i], e);
+      const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(m[i] >> 32), e);
+      const uint64_t w = ((uint64_t)hi << 32) | lo;
+      if ((w >> lane) & 1ull) col_idx[pos + __builtin_popcountll(w & below)] = 64 * e + lane;
+      pos += __builtin_popcountll(w);
+    }
+  }
+  if (order != nullptr) {
+    const int r = tid >> 3, part = tid & 7;                // row of the chunk, eighth of the head
+    const int c = r < nr ? head[r0 + r] : 0;
+    int rank = 0;
+    if (r < nr)
+      for (int t = part; t < nb; t += 8) {
+        const int ct = head[t];
+        rank += (ct > c || (ct == c && t < r0 + r)) ? 1 : 0;
+      }
+#pragma unroll
+    for (int off = 4; off >= 1; off >>= 1) rank += __shfl_xor(rank, off, 64);
+    if (r < nr && part == 0) order[base + rank] = base + r0 + r;
   }
 }
 
@@ -238,7 +501,7 @@ static void launch_rows(const Dims& s, const float* acc, float tau, uint32_t fla
                         int32_t* counts, uint64_t* masks, hipStream_t st) {
   const int rows = s.bh * s.nb, words = mask_words(s);
   const int groups = (rows + kSelWaves - 1) / kSelWaves;
-  const size_t smem = (size_t)kSelWaves * 2 * s.nb * sizeof(uint64_t);
+  const size_t smem = kSelWaves * select_row_lds(s.nb);
   const dim3 sg(groups), sb(kSelWaves * 64);
   const double dtau = (double)tau;
   if (s.nb <= 64)
@@ -254,16 +517,24 @@ static void launch_rows(const Dims& s, const float* acc, float tau, uint32_t fla
 }
 
 // counts + masks (in the workspace) -> row_ptr, col_idx, row_order.
+// Each csr group adds up the counts before its rows itself while every group
+// together reads little (groups x rows / 2 counts): one launch instead of two.
+constexpr int64_t kSumRows = 131072;
+constexpr int64_t kSumReads = (int64_t)1 << 28;
+
 static void launch_csr(const Dims& s, const int32_t* counts, const uint64_t* masks,
                        int32_t* row_ptr, int32_t* col_idx, int32_t* row_order, hipStream_t st) {
-  const int rows = s.bh * s.nb;
-  const int groups = (rows + kSelWaves - 1) / kSelWaves;
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, counts, rows, row_ptr);
-  hipLaunchKernelGGL(scatter_kernel, dim3(groups), dim3(kSelWaves * 64), 0, st, masks, row_ptr,
-                     rows, mask_words(s), col_idx);
-  if (row_order != nullptr)
-    hipLaunchKernelGGL(order_kernel, dim3(s.bh), dim3(kOrderThreads), (size_t)s.nb * sizeof(int32_t),
-                       st, counts, s.nb, row_order);
+  const int rows = s.bh * s.nb, chunks = (s.nb + kCsrRows - 1) / kCsrRows;
+  // x: heads (up to 2^31 - 1 groups), the chunks of a head in y
+  const dim3 grid(s.bh, chunks);
+  if (rows <= kSumRows && (int64_t)s.bh * chunks * rows / 2 <= kSumReads) {
+    hipLaunchKernelGGL(csr_kernel<false>, grid, dim3(1024), 0, st, counts, masks, s.nb,
+                       mask_words(s), row_ptr, col_idx, row_order);
+  } else {
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, counts, rows, row_ptr);
+    hipLaunchKernelGGL(csr_kernel<true>, grid, dim3(1024), 0, st, counts, masks, s.nb,
+                       mask_words(s), row_ptr, col_idx, row_order);
+  }
 }
 
 hipError_t launch_select(const Dims& s, const float* acc, float tau, uint32_t flags,

@@ -1,0 +1,74 @@
+"""Selection where its paths meet: sums by digit against ranked rows (masses
+whose fp64 sums round, negative and infinite ones, ties at the cut, light
+masses few and many), chunk edges of the CSR kernel, and row counts past the
+one-launch limit.  Bit for bit the oracle's."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import wise_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+def masses(kind, rows, nb, rng):
+    x = rng.random((rows, nb)).astype(np.float32)
+    if kind == "wide":          # exponents over 2^-60 .. 1: light masses in most rows
+        x *= np.exp2(-rng.integers(0, 60, (rows, nb))).astype(np.float32)
+    elif kind == "light":       # one heavy block, the others below 2^-32: more than 64 light ones where nb allows
+        x *= np.float32(2.0 ** -33)
+        x[np.arange(rows), rng.integers(0, nb, rows) * (np.arange(rows) % nb) // nb] = 1.0
+    elif kind == "ties":        # few distinct values, zeros among them
+        x = rng.integers(0, 4, (rows, nb)).astype(np.float32) * np.float32(0.125)
+    elif kind == "denormal":
+        x = (rng.integers(0, 3, (rows, nb)) * np.float32(1e-45)).astype(np.float32)
+    elif kind == "odd":         # negative and infinite masses, minus zero
+        x[::3, ::2] *= -1
+        x[1::5, 1::3] = -0.0
+        x[2::7, 0] = np.inf
+    elif kind == "peaked":
+        x = (x ** 40).astype(np.float32)
+    return x
+
+
+@pytest.mark.parametrize("kind", ["plain", "wide", "light", "ties", "denormal", "odd", "peaked"])
+@pytest.mark.parametrize("nb", [1, 2, 64, 127, 129, 300, 1024])
+def test_selection_paths(gpu_lib, kind, nb):
+    w = gpu_lib
+    heads = 3 if nb < 1024 else 1
+    rng = np.random.default_rng(nb * 31 + len(kind))
+    acc = masses(kind, heads * nb, nb, rng).reshape(1, heads, nb, nb)
+    s = w.make_shape(1, heads, 64 * nb, 64, 64)
+    sched = w.Schedule(s)
+    for tau, flags in ((0.95, 3), (0.5, 0), (1.0, 0), (0.9999999, 2)):
+        tau = float(np.float32(tau))
+        sched.select(torch.from_numpy(acc).cuda(), tau, flags)
+        torch.cuda.synchronize()
+        with np.errstate(invalid="ignore"):
+            rp, ci = O.select_support(acc.astype(np.float64), tau, flags)
+        assert np.array_equal(sched.row_ptr.cpu().numpy(), rp), (kind, nb, tau, flags)
+        assert np.array_equal(sched.col_idx[: len(ci)].cpu().numpy(), ci), (kind, nb, tau, flags)
+        assert np.array_equal(sched.row_order.cpu().numpy(), O.schedule_order(rp, nb))
+
+
+@pytest.mark.parametrize("heads,nb", [(8200, 16), (70, 3), (1, 1024)])
+def test_csr_of_many_rows(gpu_lib, heads, nb):
+    """131200 rows (past the limit of the sums in the CSR kernel), row counts 4 does not divide."""
+    w = gpu_lib
+    rng = np.random.default_rng(heads)
+    s = w.make_shape(1, heads, 64 * nb, 64, 64)
+    words = w.wise_mask_words(s)
+    m = rng.integers(0, 1 << 63, (heads * nb, words), dtype=np.int64)
+    sched = w.Schedule(s)
+    sched.from_masks(torch.from_numpy(m).cuda(), 1, 3)
+    torch.cuda.synchronize()
+    bits = np.unpackbits(m.view(np.uint8).reshape(heads * nb, words * 8), axis=1, bitorder="little")[:, :nb].astype(bool)
+    qb = np.arange(heads * nb) % nb
+    bits &= np.arange(nb)[None, :] <= qb[:, None]
+    bits[:, 0] = True
+    bits[np.arange(heads * nb), qb] = True
+    rp = np.concatenate(([0], bits.sum(1).cumsum())).astype(np.int32)
+    assert np.array_equal(sched.row_ptr.cpu().numpy(), rp)
+    assert np.array_equal(sched.col_idx[: rp[-1]].cpu().numpy(), np.nonzero(bits)[1])
+    assert np.array_equal(sched.row_order.cpu().numpy(), O.schedule_order(rp, nb))
