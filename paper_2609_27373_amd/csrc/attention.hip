@@ -1025,111 +1025,198 @@ sparse_group_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
 
 // ---------------------------------------------------------------------------
 // Block-sparse attention for 16-key blocks.  One one-wave work-group per
-// (batch, head, query block) row, as for 32-key blocks; the row's 16 queries
-// fill both halves of the wave's 32 MFMA columns (lanes n and n + 16 hold the
-// same query, and only the first copy is written).  A 32-key tile is any two
-// consecutive blocks of the row's support, staged as LDS rows 0-15 and
-// 16-31, so every tile key belongs to the row; a last tile with one block
-// stages it twice and masks the copy.
+// (batch, head, query block) row on v_mfma_f32_16x16x32_bf16, whose 16 columns
+// are the row's 16 queries.  A tile is any two consecutive blocks of the row's
+// support.  S^T = K Q^T block by block, so lane 16 g + n holds keys
+// 4 g .. 4 g + 3 of either block for query n: the two fours are the 8
+// consecutive B entries of O^T = V^T P^T with the tile's keys taken in the
+// order 4 g of a, 4 g of b, g = 0 .. 3, which the rows of the transposing V
+// reads follow.  K and V are copied straight into LDS, one tile each (12 KB at
+// d 96): the next tile's K as soon as this one's is in registers, its V after
+// PV, so each has half a tile of work to land and 13 waves fit a CU.  A last
+// tile with one block takes it twice and masks the copy.
+//
+// Bound by the L2: every row reads its own K and V (12.7 GB at 4096 x 220
+// heads, d 96, density 0.23, 94% L2 hits) at 22 TB/s, where contiguous copies
+// from L2 alone reach 25-32.  843 -> 556 us there and 348 -> 262 us at 192
+// grouped heads of 64, against 32x32x16 MFMAs with the queries held twice and
+// tiles staged through registers; K read straight into registers (64-byte
+// pieces of rows, half the L2 rate) took 664 and 400 us.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 128 ? 3 : 4)))
 sparse_row16_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
                     const uint16_t* __restrict__ V, const int32_t* __restrict__ row_ptr,
                     const int32_t* __restrict__ col_idx, const int32_t* __restrict__ order,
                     uint16_t* __restrict__ O, float* __restrict__ lse, int n, int nb, int rows,
                     int heads, int gq, Sched sc, float c) {
-  using G = Geo<D>;
-  constexpr int kRowChunks = D / 8;                 // 16-byte chunks per key row
-  constexpr int kPer = 32 * kRowChunks / 64;        // chunks per lane and tensor
-  __shared__ __attribute__((aligned(16))) uint16_t ks[32 * G::kKStride];
-  __shared__ __attribute__((aligned(16))) uint16_t vt[32 * G::kVStride];
+  constexpr int kC = D / 32;                        // MFMAs of a block's S^T; 1 KB copies of its V
+  constexpr int kT = D / 16;                        // MFMAs of PV
+  constexpr int kRow = 2 * D, kBlock = 16 * kRow;   // bytes
+  __shared__ __attribute__((aligned(1024))) char kt[2 * kBlock], vt[2 * kBlock];
   int sh, sit;
   if (!sched_slot(sc, sh, sit)) return;
   const int row = order ? order[sh * nb + sit] : sh * nb + (nb - 1 - sit);
   if ((unsigned)row >= (unsigned)rows) return;
   const int bh = row / nb, qb = row % nb;
   const size_t hoff = (size_t)bh * n * D;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x, g = lane >> 4, ln = lane & 15;
   const int q0 = 16 * qb;
   const size_t kvoff = (size_t)kv_head(bh, heads, gq) * n * D;
-  const __amdgpu_buffer_rsrc_t rk = buffer_rsrc(K + kvoff), rv = buffer_rsrc(V + kvoff);
+  const u32x4_t bk = buffer_words(K + kvoff), bv = buffer_words(V + kvoff);
+  const uint32_t lk = lds_address(kt), lv = lds_address(vt);
 
-  // The row's valid ids (0..qb) in order; the last can be the diagonal.
+  // The row's valid ids (0..qb) in order, 64 at a time in `ids`; the last of
+  // all can be the diagonal.
   int e = row_ptr[row];
   const int end = row_ptr[row + 1];
+  int ids = 0;
+  uint64_t left = 0;
   auto next_id = [&]() {
-    while (e < end) {
-      const int kb = col_idx[e++];
-      if ((unsigned)kb <= (unsigned)qb) return kb;
+    while (left == 0) {
+      if (e >= end) return -1;
+      ids = e + lane < end ? col_idx[e + lane] : -1;
+      left = __builtin_amdgcn_ballot_w64((unsigned)ids <= (unsigned)qb);
+      e += 64;
     }
-    return -1;
+    const int at = __builtin_ctzll(left);
+    left &= left - 1;
+    return (int)__builtin_amdgcn_readlane(ids, at);
   };
-  // Tile: blocks a and b (b < 0: a alone).
-  auto next_tile = [&](int& a, int& b) {
+  auto next_tile = [&](int& a, int& b) {             // b < 0: a alone
     a = next_id();
     b = a < 0 ? -1 : next_id();
     return a >= 0;
   };
 
-  WaveRows<D> w;
-  {
-    const uint16_t* qr = Q + hoff + (size_t)(q0 + (lane & 15)) * D + 8 * (lane >> 5);
+  u32x4_t qf[kC];
+  const uint16_t* qr = Q + hoff + (size_t)(q0 + ln) * D + 8 * g;
 #pragma unroll
-    for (int cc = 0; cc < G::kDChunks; ++cc) w.qf[cc] = *(const u32x4_t*)(qr + 16 * cc);
-  }
-  w.reset();
-  // Staging: chunk i of this lane is key row r_i (0..31) of the tile, dims
-  // 8 * (ch % kRowChunks); rows 0-15 come from block a, 16-31 from block b
-  // (from a again when the tile has one block).
-  u32x4_t kr[kPer], vr[kPer];
-  auto load = [&](int a, int b) {
-    const int bb = b < 0 ? a : b;
+  for (int i = 0; i < kC; ++i) qf[i] = *(const u32x4_t*)(qr + 32 * i);
+  f32x4_t o[kT];
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int ch = lane + 64 * i, r = ch / kRowChunks;
-      const int key = (r < 16 ? 16 * a : 16 * bb - 16) + r;
-      const uint32_t off = (uint32_t)(key * D + (ch % kRowChunks) * 8) * 2;
-      kr[i] = buffer_load16(rk, off, 0);
-      vr[i] = buffer_load16(rv, off, 0);
-    }
+  for (int t = 0; t < kT; ++t) o[t] = f32x4_t{};
+  float m = -INFINITY, l = 0.f;
+
+  // V rows in LDS: 32-byte pieces permuted by row, so that the 8 rows a half
+  // wave reads 32 bytes of fall on distinct banks.
+  auto piece = [](int r, int p) {
+    return D == 128 ? p ^ (r & 7) : D == 96 ? p ^ ((r >> 2) & 1) : p ^ ((r >> 1) & 3);
   };
-  auto store = [&]() {
+  uint32_t ko[kC], vo[kC];                          // source bytes of this lane's copies in a block
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int ch = lane + 64 * i, r = ch / kRowChunks, c8 = (ch % kRowChunks) * 8;
-      *(u32x4_t*)(ks + k_lds_row(r) * G::kKStride + c8) = kr[i];
-      *(u32x4_t*)(vt + r * G::kVStride + c8) = vr[i];
-    }
+  for (int i = 0; i < kC; ++i) {
+    const int at = 1024 * i + 16 * lane, r = at / kRow, ch = at % kRow / 16;
+    ko[i] = r * kRow + Swizzle<D>::k_chunk(r, ch) * 16;
+    vo[i] = r * kRow + piece(r, ch >> 1) * 32 + (ch & 1) * 16;
+  }
+  const int vr = 4 * g + ((lane >> 2) & 3);         // row of this lane's transposing reads
+  uint32_t ka[kC], va[kT];
+#pragma unroll
+  for (int i = 0; i < kC; ++i) ka[i] = ln * kRow + Swizzle<D>::k_chunk(ln, 4 * i + g) * 16;
+#pragma unroll
+  for (int t = 0; t < kT; ++t) va[t] = vr * kRow + piece(vr, t) * 32 + 8 * (lane & 3);
+
+  auto copy = [&](u32x4_t r, const uint32_t off[kC], int x, int y, uint32_t lds) {
+    const uint32_t sx = (uint32_t)x * kBlock, sy = (uint32_t)(y < 0 ? x : y) * kBlock;
+#pragma unroll
+    for (int i = 0; i < kC; ++i) copy16_to_lds(r, off[i], sx, lds + 1024 * i);
+#pragma unroll
+    for (int i = 0; i < kC; ++i) copy16_to_lds(r, off[i], sy, lds + kBlock + 1024 * i);
   };
 
   int a = -1, b = -1, an = -1, bn = -1;
   bool have = next_tile(a, b);
-  if (have) load(a, b);
-  const int qi = q0 + (lane & 15), h = lane >> 5;
-  while (have) {
-    store();
-    __syncthreads();
-    const bool more = next_tile(an, bn);
-    if (more) load(an, bn);
-    f32x16_t sc[1];
-    w.template scores<1>(ks, lane, sc);
-    if (!more) {
-      // the last tile: the diagonal block (if present) and a masked copy
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int blk = r < 8 ? a : b;
-        const int key = 16 * blk + 8 * h + (r & 7);
-        if (blk < 0 || key > qi) sc[0][r] = -INFINITY;
+  for (int i = 0; i < kC; ++i) asm volatile("" : "+v"(qf[i]));   // Q has landed: only copies count below
+  if (have) {
+    copy(bk, ko, a, b, lk);
+    copy(bv, vo, a, b, lv);
+  }
+  const int qi = q0 + ln;
+  while (have) {
+    const bool more = next_tile(an, bn);
+    wait_copies<2 * kC>();                          // this tile's K; its V may be in flight
+    u32x4_t kf[2][kC];
+#pragma unroll
+    for (int i = 0; i < kC; ++i)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) kf[u][i] = *(const u32x4_t*)(kt + ka[i] + u * kBlock);
+    f32x4_t s[2] = {f32x4_t{}, f32x4_t{}};
+#pragma unroll
+    for (int i = 0; i < kC; ++i)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) s[u] = mfma16x16x32(kf[u][i], qf[i], s[u]);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // K read: its place is free
+    if (more) copy(bk, ko, an, bn, lk);
+    if (!more) {   // the last tile: the diagonal block (if present) and a masked copy
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int blk = u ? b : a;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (blk < 0 || 16 * blk + 4 * g + i > qi) s[u][i] = -INFINITY;
       }
     }
-    w.template softmax_pv<1>(sc, vt, lane, c);
-    __syncthreads();
+    float mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[u][i]);
+    mx = quad_max(mx) * c;
+    const bool grow = mx > m;
+    if (__builtin_amdgcn_ballot_w64(grow)) {
+      const float mn = grow ? mx : m;
+      const float alpha = (mn == m) ? 1.f : fast_exp2(m - mn);
+      l *= alpha;
+#pragma unroll
+      for (int t = 0; t < kT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("v_mul_f32 %0, %0, %1" : "+v"(o[t][i]) : "v"(alpha));
+      m = mn;
+    }
+    const float mb = (m == -INFINITY) ? 0.f : m;
+    u32x4_t pb;
+    float ts = 0.f;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s[u][i] = fast_exp2(__builtin_fmaf(s[u][i], c, -mb));
+        ts += s[u][i];
+      }
+      pb[2 * u] = pack_bf16x2(s[u][0], s[u][1]);
+      pb[2 * u + 1] = pack_bf16x2(s[u][2], s[u][3]);
+    }
+    l += ts;
+    if (more) wait_copies<2 * kC>();                // this tile's V; the next K may be in flight
+    else wait_copies<0>();
+#pragma unroll
+    for (int t = 0; t < kT; ++t) {
+      const u32x2_t lo = lds_read_tr16((const uint16_t*)(vt + va[t]));
+      const u32x2_t hi = lds_read_tr16((const uint16_t*)(vt + va[t] + kBlock));
+      o[t] = mfma16x16x32(u32x4_t{lo[0], lo[1], hi[0], hi[1]}, pb, o[t]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // V read: its place is free
+    if (more) copy(bv, vo, an, bn, lv);
     a = an;
     b = bn;
     have = more;
   }
-  w.finish(O + hoff, lse ? lse + (size_t)bh * n : nullptr, q0, lane, 16);
+  const float lt = quad_sum(l);
+  const float inv = lt > 0.f ? 1.f / lt : 0.f;
+  uint16_t* orow = O + hoff + (size_t)qi * D + 4 * g;
+#pragma unroll
+  for (int t = 0; t < kT; ++t) {
+    u32x2_t w;
+    w[0] = pack_bf16x2(o[t][0] * inv, o[t][1] * inv);
+    w[1] = pack_bf16x2(o[t][2] * inv, o[t][3] * inv);
+    *(u32x2_t*)(orow + 16 * t) = w;
+  }
+  if (lse != nullptr && g == 0)
+    lse[(size_t)bh * n + qi] = lt > 0.f ? (m + __builtin_log2f(lt)) * kLn2 : -INFINITY;
 }
 
 // ---------------------------------------------------------------------------
