@@ -6,12 +6,13 @@
 //                       (Section 5.1, eq. block_attention_mass)
 //   sparse_attn_kernel  attention restricted to a CSR block support
 //   sparse_group_kernel (Section 5.2, eq. wise_attention): one work-group
-//   sparse_row16_kernel per row; groups of consecutive rows over the union
-//                       of their supports (the same outputs, for dense
-//                       supports); one wave per row of 16-key blocks
+//   sparse_row32_kernel per row (64- and 128-key blocks); groups of
+//   sparse_row16_kernel consecutive rows over the union of their supports
+//                       (the same outputs, for dense supports); one wave per
+//                       row of 32- or 16-key blocks
 //
-// Shared tile engine.  A wave owns 32 consecutive queries.  For each tile of
-// 64 keys (32 for 32-key blocks) it computes S^T = K Q^T with
+// Shared tile engine (all but the 16-key kernel).  A wave owns 32 consecutive
+// queries.  For each tile of 64 keys (32 for 32-key blocks) it computes S^T = K Q^T with
 // v_mfma_f32_32x32x16_bf16 (A = K from
 // LDS, B = Q^T held in registers for the whole row), so every lane ends up
 // holding 32 scores of ONE query.  The row max needs one cross-lane step
@@ -34,20 +35,18 @@
 namespace wise {
 
 // ---------------------------------------------------------------------------
-// Global -> register -> LDS staging of one tile of KT keys (64, or 32 for
-// 32-key blocks; K rows permuted so the S^T accumulator comes out in PV
-// operand order; V rows in natural order).  Loads for the next tile are
+// Global -> register -> LDS staging of one tile of 64 keys (K rows permuted so
+// the S^T accumulator comes out in PV operand order; V rows in natural order).  Loads for the next tile are
 // issued before the current one is computed, so the memory latency hides
 // behind the MFMA work; stores go to an LDS tile no wave still reads: after
 // the barrier that retires it, or, in the 8-wave dense group, into its
 // second buffer.
 // ---------------------------------------------------------------------------
-template <int D, int NT, int KT = kKeyTile>
+template <int D, int NT>
 struct TileStage {
   using G = Geo<D>;
-  static_assert(KT == 32 || KT == 64, "key tile");
   static constexpr int kRowChunks = D / 8;                    // 16-B chunks per key row
-  static constexpr int kChunks = KT * kRowChunks;             // per tensor
+  static constexpr int kChunks = kKeyTile * kRowChunks;       // per tensor
   static constexpr int kPer = (kChunks + NT - 1) / NT;
 
   u32x4_t kr[kPer];
@@ -197,11 +196,12 @@ struct WaveRows {
         if (key0 + score_key(t, r, h) > qi) s[t][r] = -INFINITY;
   }
 
-  // Online softmax of one tile and O^T += V^T P^T.  With kParts = 2 (4) the
-  // sums of this lane's probabilities over each 32-key half (16-key quarter)
-  // of the tile are kept in hs[] (the row sum then adds the parts).
+  // Online softmax of one tile: the probabilities packed in pb, O and l
+  // rescaled.  With kParts = 2 (4) the sums of this lane's probabilities over
+  // each 32-key half (16-key quarter) of the tile are kept in hs[] (the row
+  // sum then adds the parts).
   template <int H, int kParts = 0>
-  __device__ __forceinline__ void softmax_pv(f32x16_t s[H], const uint16_t* vt, int lane, float c) {
+  __device__ __forceinline__ void softmax(f32x16_t s[H], u32x4_t pb[2 * H], float c) {
     float mx = -INFINITY;
 #pragma unroll
     for (int t = 0; t < H; ++t)
@@ -223,7 +223,6 @@ struct WaveRows {
       m = mn;
     }
     const float mb = (m == -INFINITY) ? 0.f : m;
-    u32x4_t pb[2 * H];
     // The tile's probabilities are summed on their own and added to the row
     // sum once per tile: a long row (16K keys per lane at 32K) then carries
     // rounding error ~ tiles * eps instead of ~ keys * eps.
@@ -253,9 +252,16 @@ struct WaveRows {
         for (int e = 0; e < 4; ++e)
           pb[2 * t + u][e] = pack_bf16x2(s[t][8 * u + 2 * e], s[t][8 * u + 2 * e + 1]);
     }
-    // A = V^T fragment: lane L needs V[16ks + 8(L/32) + e][32t + L%32], e = 0..7,
-    // fetched as two transpose reads of 4 keys each (see lds_read_tr16).
     l += ts;
+  }
+
+  // Softmax of one tile and O^T += V^T P^T.  A = V^T fragment: lane L needs
+  // V[16ks + 8(L/32) + e][32t + L%32], e = 0..7, fetched as two transpose
+  // reads of 4 keys each (see lds_read_tr16).
+  template <int H, int kParts = 0>
+  __device__ __forceinline__ void softmax_pv(f32x16_t s[H], const uint16_t* vt, int lane, float c) {
+    u32x4_t pb[2 * H];
+    softmax<H, kParts>(s, pb, c);
     const uint16_t* a = vt + (8 * (lane >> 5) + ((lane >> 2) & 3)) * G::kVStride +
                         16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 #pragma unroll
@@ -534,13 +540,9 @@ constexpr int kMassBatch = 16;    // entry loads in flight per half-wave in the 
 
 // Waves per SIMD the register allocator must leave room for.  Two by default
 // (the d-128 tiles hold 190-250 VGPRs).  The four-wave dense group at d 96
-// and the one-wave 32-key sparse group at d 96 fit in 168 VGPRs (three
-// waves), the 32-key sparse group at d 64 in 128 (four): more resident waves
-// hide more of each one's staging latency (2-6% on those kernels).
+// fits in 168 VGPRs (three waves): more resident waves hide more of each
+// one's staging latency (2-6%).
 constexpr int dense_waves_per_simd(int d, int nw) { return d == 96 && nw == 4 ? 3 : 2; }
-constexpr int sparse_waves_per_simd(int d, int kt) {
-  return kt != 32 ? 2 : d == 64 ? 4 : d == 96 ? 3 : 2;
-}
 
 template <int D, int NW, int BM>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd(D, NW))))
@@ -777,25 +779,25 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
 
 // ---------------------------------------------------------------------------
 // Block-sparse attention over a CSR support.  One work-group per (batch,
-// head, query block) row, NW = block/32 waves; key tiles of KT = min(block,
-// 64) keys, so a 32-key block is one 32-key tile and a one-wave group.
+// head, query block) row of 64- or 128-key blocks, NW = block/32 waves, in
+// tiles of 64 keys.
 // Schedule slot s (a logical id, contiguous per XCD) runs row order[s];
 // wise_select_support writes the rows of each head together, longest support
 // first, so an XCD works through a few heads at a time and their K/V tiles
 // stay in its L2.
 // ---------------------------------------------------------------------------
-template <int D, int NW, int KT>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sparse_waves_per_simd(D, KT))))
+template <int D, int NW>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
 sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
                    const uint16_t* __restrict__ V, const int32_t* __restrict__ row_ptr,
                    const int32_t* __restrict__ col_idx, const int32_t* __restrict__ order,
                    uint16_t* __restrict__ O, float* __restrict__ lse, int n, int nb, int rows,
                    int heads, int gq, Sched sc, float c) {
   using G = Geo<D>;
-  constexpr int kNT = NW * 64, kB = NW * 32, kTPB = kB / KT, kH = KT / 32;
-  static_assert(kTPB >= 1 && kB % KT == 0, "block / key tile");
-  __shared__ __attribute__((aligned(16))) uint16_t ks[KT * G::kKStride];
-  __shared__ __attribute__((aligned(16))) uint16_t vt[KT * G::kVStride];
+  constexpr int kNT = NW * 64, kB = NW * 32, kTPB = kB / kKeyTile;
+  static_assert(kTPB >= 1 && kB % kKeyTile == 0, "block / key tile");
+  __shared__ __attribute__((aligned(16))) uint16_t ks[G::kKElems];
+  __shared__ __attribute__((aligned(16))) uint16_t vt[G::kVElems];
   int sh, sit;
   if (!sched_slot(sc, sh, sit)) return;
   const int row = order ? order[sh * nb + sit] : sh * nb + (nb - 1 - sit);
@@ -818,13 +820,13 @@ sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
   auto tile_key = [&](int it, bool& ok) {
     const int kb = col_idx[beg + it / kTPB];
     ok = (unsigned)kb <= (unsigned)qb;
-    return ok ? kb * kB + (it % kTPB) * KT : 0;
+    return ok ? kb * kB + (it % kTPB) * kKeyTile : 0;
   };
 
   WaveRows<D> w;
   w.load_q(Q + hoff, q0, lane);
   w.reset();
-  TileStage<D, kNT, KT> st;
+  TileStage<D, kNT> st;
   const int ntiles = nent * kTPB;
   // Entries are ascending, so only the last one can be the diagonal block:
   // every earlier tile lies wholly below this group's queries.
@@ -838,7 +840,7 @@ sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
     bool ok_next;
     const int key_next = tile_key(it + 1, ok_next);
     st.load(rk, rv, key_next, tid);
-    if (ok && key0 + KT - 1 < qb * kB) w.template attend<false, kH>(ks, vt, lane, c, key0, q0);
+    if (ok && key0 + kKeyTile - 1 < qb * kB) w.template attend<false>(ks, vt, lane, c, key0, q0);
     __syncthreads();
     key0 = key_next;
     ok = ok_next;
@@ -849,7 +851,7 @@ sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
     bool ok_next = false;
     const int key_next = (it + 1 < ntiles) ? tile_key(it + 1, ok_next) : 0;
     if (it + 1 < ntiles) st.load(rk, rv, key_next, tid);
-    if (ok && key0 <= q0) w.template attend<true, kH>(ks, vt, lane, c, key0, q0);
+    if (ok && key0 <= q0) w.template attend<true>(ks, vt, lane, c, key0, q0);
     __syncthreads();
     key0 = key_next;
     ok = ok_next;
@@ -1024,6 +1026,128 @@ sparse_group_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
 }
 
 // ---------------------------------------------------------------------------
+// A support row's valid ids (0..qb) in order, 64 read at a time; ids outside
+// are skipped.  Everything but `ids` is wave-uniform.
+// ---------------------------------------------------------------------------
+struct RowIds {
+  const int32_t* col_idx;
+  int e, end, qb, ids;
+  uint64_t left;
+  __device__ __forceinline__ RowIds(const int32_t* row_ptr, const int32_t* ci, int row, int qb_)
+      : col_idx(ci), e(row_ptr[row]), end(row_ptr[row + 1]), qb(qb_), ids(0), left(0) {}
+  __device__ __forceinline__ int next(int lane) {    // -1: no more
+    while (left == 0) {
+      if (e >= end) return -1;
+      ids = e + lane < end ? col_idx[e + lane] : -1;
+      left = __builtin_amdgcn_ballot_w64((unsigned)ids <= (unsigned)qb);
+      e += 64;
+    }
+    const int at = __builtin_ctzll(left);
+    left &= left - 1;
+    return (int)__builtin_amdgcn_readlane(ids, at);
+  }
+};
+
+// ---------------------------------------------------------------------------
+// Block-sparse attention for 32-key blocks: one one-wave work-group per
+// (batch, head, query block) row, a tile per block.  K and V are copied
+// straight into LDS, one tile each (12 KB at d 96): the next tile's K as soon
+// as this one's is in registers, its V after PV, so each has half a tile of
+// work to land, and no registers hold tiles in flight (124 VGPRs at d 96, 102
+// at d 64: LDS decides how many waves fit a CU).  The online softmax groups
+// keys in 32s, so a full support does not reproduce the dense kernel's bits.
+//
+// Bound by the L2, which serves 10.4 GB at 4096 x 220 heads, d 96, density
+// 0.36, at 21 TB/s (25-32 for contiguous copies alone), and by what the SIMDs
+// leave of each other's waits.  Against tiles staged through registers (one
+// more tile of 48 VGPRs in flight, LDS written by the wave): 536 -> 496 us
+// there, 276 -> 259 us at 192 grouped heads of 64, 182 -> 153 us at 32 heads
+// of 128.
+// ---------------------------------------------------------------------------
+template <int D>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : D == 96 ? 3 : 2)))
+sparse_row32_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+                    const uint16_t* __restrict__ V, const int32_t* __restrict__ row_ptr,
+                    const int32_t* __restrict__ col_idx, const int32_t* __restrict__ order,
+                    uint16_t* __restrict__ O, float* __restrict__ lse, int n, int nb, int rows,
+                    int heads, int gq, Sched sc, float c) {
+  using G = Geo<D>;
+  constexpr int kC = D / 32;                        // 1 KB copies per 16 rows
+  constexpr int kRow = 2 * D, kTile = 32 * kRow;    // bytes
+  __shared__ __attribute__((aligned(1024))) char kt[kTile], vt[kTile];
+  int sh, sit;
+  if (!sched_slot(sc, sh, sit)) return;
+  const int row = order ? order[sh * nb + sit] : sh * nb + (nb - 1 - sit);
+  if ((unsigned)row >= (unsigned)rows) return;
+  const int bh = row / nb, qb = row % nb;
+  const size_t hoff = (size_t)bh * n * D;
+  const int lane = threadIdx.x, q0 = 32 * qb;
+  const size_t kvoff = (size_t)kv_head(bh, heads, gq) * n * D;
+  const u32x4_t bk = buffer_words(K + kvoff), bv = buffer_words(V + kvoff);
+  const uint32_t lk = lds_address(kt), lv = lds_address(vt);
+  RowIds ids(row_ptr, col_idx, row, qb);
+
+  WaveRows<D> w;
+  w.load_q(Q + hoff, q0, lane);
+  w.reset();
+  ReadAddr<D> ra;
+  ra.init(lane);
+  uint32_t ko[kC], vo[kC];                          // source bytes of this lane's copies in 16 rows
+#pragma unroll
+  for (int i = 0; i < kC; ++i) {
+    const int at = 1024 * i + 16 * lane, r = at / kRow, ch = at % kRow / 16;
+    ko[i] = k_lds_row(r) * kRow + Swizzle<D>::k_chunk(r, ch) * 16;
+    vo[i] = r * kRow + (Swizzle<D>::v_block(r, ch >> 2) * 4 + (ch & 3)) * 16;
+  }
+  auto copy = [&](u32x4_t r, const uint32_t off[kC], int kb, uint32_t lds) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int i = 0; i < kC; ++i)
+        copy16_to_lds(r, off[i], (uint32_t)(2 * kb + u) * 16 * kRow, lds + 1024 * (u * kC + i));
+  };
+  int kb = ids.next(lane);
+#pragma unroll
+  for (int i = 0; i < G::kDChunks; ++i) asm volatile("" : "+v"(w.qf[i]));   // Q has landed: only copies count below
+  if (kb >= 0) {
+    copy(bk, ko, kb, lk);
+    copy(bv, vo, kb, lv);
+  }
+  while (kb >= 0) {
+    const int next = ids.next(lane);
+    wait_copies<2 * kC>();                          // this tile's K; its V may be in flight
+    u32x4_t kf[G::kDChunks];
+#pragma unroll
+    for (int i = 0; i < G::kDChunks; ++i) kf[i] = *(const u32x4_t*)(kt + ra.k[i]);
+    f32x16_t s[1] = {f32x16_t{}};
+#pragma unroll
+    for (int i = 0; i < G::kDChunks; ++i) s[0] = mfma32x32x16(kf[i], w.qf[i], s[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // K read: its place is free
+    if (next >= 0) copy(bk, ko, next, lk);
+    if (kb == qb) WaveRows<D>::template mask<1>(s, q0, q0 + (lane & 31), lane);
+    u32x4_t pb[2];
+    w.template softmax<1>(s, pb, c);
+    if (next >= 0) wait_copies<2 * kC>();           // this tile's V; the next K may be in flight
+    else wait_copies<0>();
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int t = 0; t < G::kDTiles; ++t) {
+        const char* p = vt + ra.v[t] + 16 * ks * kRow;
+        const u32x2_t lo = lds_read_tr16((const uint16_t*)p);
+        const u32x2_t hi = lds_read_tr16((const uint16_t*)(p + 4 * kRow));
+        w.o[t] = mfma32x32x16(u32x4_t{lo[0], lo[1], hi[0], hi[1]}, pb[ks], w.o[t]);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // V read: its place is free
+    if (next >= 0) copy(bv, vo, next, lv);
+    kb = next;
+  }
+  w.finish(O + hoff, lse ? lse + (size_t)bh * n : nullptr, q0, lane);
+}
+
+// ---------------------------------------------------------------------------
 // Block-sparse attention for 16-key blocks.  One one-wave work-group per
 // (batch, head, query block) row on v_mfma_f32_16x16x32_bf16, whose 16 columns
 // are the row's 16 queries.  A tile is any two consecutive blocks of the row's
@@ -1066,26 +1190,10 @@ sparse_row16_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
   const u32x4_t bk = buffer_words(K + kvoff), bv = buffer_words(V + kvoff);
   const uint32_t lk = lds_address(kt), lv = lds_address(vt);
 
-  // The row's valid ids (0..qb) in order, 64 at a time in `ids`; the last of
-  // all can be the diagonal.
-  int e = row_ptr[row];
-  const int end = row_ptr[row + 1];
-  int ids = 0;
-  uint64_t left = 0;
-  auto next_id = [&]() {
-    while (left == 0) {
-      if (e >= end) return -1;
-      ids = e + lane < end ? col_idx[e + lane] : -1;
-      left = __builtin_amdgcn_ballot_w64((unsigned)ids <= (unsigned)qb);
-      e += 64;
-    }
-    const int at = __builtin_ctzll(left);
-    left &= left - 1;
-    return (int)__builtin_amdgcn_readlane(ids, at);
-  };
-  auto next_tile = [&](int& a, int& b) {             // b < 0: a alone
-    a = next_id();
-    b = a < 0 ? -1 : next_id();
+  RowIds ids(row_ptr, col_idx, row, qb);            // the last valid id can be the diagonal
+  auto next_tile = [&](int& a, int& b) {            // b < 0: a alone
+    a = ids.next(lane);
+    b = a < 0 ? -1 : ids.next(lane);
     return a >= 0;
   };
 
@@ -1300,13 +1408,13 @@ static hipError_t launch_sparse_d(const Dims& s, const void* q, const void* k, c
     hipLaunchKernelGGL((sparse_row16_kernel<D>), grid, dim3(64), 0, st, Q, K, V, rp, ci, order,
                        (uint16_t*)o, lse, s.n, s.nb, rows, s.heads, s.gq, sc, c);
   else if (s.block == 32)
-    hipLaunchKernelGGL((sparse_attn_kernel<D, 1, 32>), grid, dim3(64), 0, st, Q, K, V, rp, ci,
-                       order, (uint16_t*)o, lse, s.n, s.nb, rows, s.heads, s.gq, sc, c);
+    hipLaunchKernelGGL((sparse_row32_kernel<D>), grid, dim3(64), 0, st, Q, K, V, rp, ci, order,
+                       (uint16_t*)o, lse, s.n, s.nb, rows, s.heads, s.gq, sc, c);
   else if (s.block == 64)
-    hipLaunchKernelGGL((sparse_attn_kernel<D, 2, 64>), grid, dim3(128), 0, st, Q, K, V, rp, ci,
+    hipLaunchKernelGGL((sparse_attn_kernel<D, 2>), grid, dim3(128), 0, st, Q, K, V, rp, ci,
                        order, (uint16_t*)o, lse, s.n, s.nb, rows, s.heads, s.gq, sc, c);
   else
-    hipLaunchKernelGGL((sparse_attn_kernel<D, 4, 64>), grid, dim3(256), 0, st, Q, K, V, rp, ci,
+    hipLaunchKernelGGL((sparse_attn_kernel<D, 4>), grid, dim3(256), 0, st, Q, K, V, rp, ci,
                        order, (uint16_t*)o, lse, s.n, s.nb, rows, s.heads, s.gq, sc, c);
   return hipGetLastError();
 }

@@ -1,4 +1,4 @@
-"""16-key-block rows whose ids come 64 at a time: row lengths around that
+"""16- and 32-key-block rows whose ids come 64 at a time: row lengths around that
 batch, one and two blocks in the last tile, ids to skip at batch edges, and
 rows with none, against the oracle."""
 
@@ -12,10 +12,11 @@ from parity_util import assert_attn, assert_lse, f64
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("B", [16, 32])
 @pytest.mark.parametrize("d,kv_heads", [(64, 1), (96, 2), (128, 2)])
-def test_row16_id_batches(gpu_lib, d, kv_heads):
+def test_one_wave_rows_id_batches(gpu_lib, d, kv_heads, B):
     w = gpu_lib
-    n, B, h = 2112, 16, 2
+    n, h = 132 * B, 2
     nb = n // B
     g = torch.Generator().manual_seed(d)
     q = (torch.randn((1, h, n, d), generator=g) * 1.5).to(torch.bfloat16)
