@@ -28,6 +28,7 @@
 //
 // Work order: see sched_slot (heaviest items of every head first, heads
 // grouped per XCD).
+#include <algorithm>
 #include <type_traits>
 
 #include "wise_device.hpp"
@@ -313,7 +314,7 @@ struct WaveRows {
 
   static constexpr int kAhead = 4;               // LDS fragments in flight
 
-  // One step of the software pipeline of the 8-wave dense group: S^T of the
+  // One step of the software pipeline of the dense groups: S^T of the
   // next tile (kQk: into sn, from its K tile kn, masked by maskn) and online
   // softmax and PV of the current one (kPv: its masked scores s, their max mx,
   // its V tile vt).  The same operations in the same order as attend(), so the
@@ -538,14 +539,20 @@ struct WaveRows {
 constexpr int kMassChunk = 256;   // workspace entries reduced per epilogue pass
 constexpr int kMassBatch = 16;    // entry loads in flight per half-wave in the epilogue
 
-// Waves per SIMD the register allocator must leave room for.  Two by default
-// (the d-128 tiles hold 190-250 VGPRs).  The four-wave dense group at d 96
-// fits in 168 VGPRs (three waves): more resident waves hide more of each
-// one's staging latency (2-6%).
-constexpr int dense_waves_per_simd(int d, int nw) { return d == 96 && nw == 4 ? 3 : 2; }
+// Tiles in each LDS ring of the dense group (0: one tile, staged through
+// registers).  An 8-wave group fills its CU alone, so its copies get two steps
+// to land; two 4-wave groups (and at d 64 five) share a CU and cover each
+// other's waits, and four tiles each would leave one (d 96: 1242 us instead of
+// 796 at 8192 x 55 heads).  Rings against the staged loop, 4-wave groups: d 96,
+// 8192 x 55 heads 822 -> 796 us, with masses 890 -> 841, 1088 x 8 heads 21.7 ->
+// 19.8; d 64, 4096 x 192 grouped heads 506 -> 491, with 32-key masses 596 ->
+// 570; d 128, 640 x 4 heads 17.8 -> 15.5.  2-wave groups (lengths 128 does not
+// divide) stay staged: eight copies per wave and tile cost its two waves more
+// than the staging (1216 x 15 heads of 64: 24.0 against 22.0 us).
+constexpr int dense_ring(int nw) { return nw == 8 ? 4 : nw == 4 ? 2 : 0; }
 
 template <int D, int NW, int BM>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(dense_waves_per_simd(D, NW))))
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
 dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
                   const uint16_t* __restrict__ V, uint16_t* __restrict__ O,
                   float* __restrict__ lse, int n, int heads, int gq, Sched sc, float c,
@@ -556,12 +563,8 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
   constexpr int kE = BM > 0 && BM < 64 ? BM : 64;   // keys per workspace entry
   constexpr int kEPT = kKeyTile / kE;               // entries per 64-key tile
   constexpr int kParts = kMass ? (kE == 16 ? 4 : 2) : 0;
-  // An 8-wave group fills its CU alone (two waves per SIMD), so no other
-  // group runs while it waits: it runs the software pipeline of step() on
-  // rings of LDS tiles, one barrier per tile.  Smaller groups share a CU three
-  // or four at a time; they stage and compute around two barriers.
-  constexpr int kBufs = NW == 8 ? 2 : 1;
-  constexpr int kLds = kBufs == 2 ? 8 * Swizzle<D>::kTile : 2 * (G::kKElems + G::kVElems);
+  constexpr int R = dense_ring(NW);
+  constexpr int kLds = R > 0 ? 2 * R * Swizzle<D>::kTile : 2 * (G::kKElems + G::kVElems);
   __shared__ __attribute__((aligned(1024))) char smem[kLds];
   uint16_t* const ks = (uint16_t*)smem;
   uint16_t* const vt = ks + G::kKElems;
@@ -600,14 +603,14 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
   const int ntiles = (qbase + kQT) / kKeyTile;
   const int nfull = qbase / kKeyTile;
   TileStage<D, kNT> st;
-  if constexpr (kBufs == 1) st.load(rk, rv, 0, tid);
-  if constexpr (kBufs == 2) {
+  if constexpr (R == 0) st.load(rk, rv, 0, tid);
+  if constexpr (R > 0) {
     // Software pipeline: in step `it` a wave computes S^T of tile it+1 and
-    // softmax and PV of tile it, while K(it+4) and V(it+3) are copied into
-    // rings of four K and four V tiles (128 KB of LDS; registers already
-    // limit a CU to one of these groups).  Copies have two steps to land: one
-    // step is less than the latency of a tile from HBM (16K: 1.01x instead of
-    // 1.06x of the unpipelined loop).  Measured against that loop (S^T,
+    // softmax and PV of tile it, while K(it+R) and V(it+R-1) are copied into
+    // rings of R K and R V tiles.  At d 128, R = 4 (128 KB of LDS; registers
+    // already limit a CU to one 8-wave group), copies have two steps to land:
+    // one step is less than the latency of a tile from HBM (16K: 1.01x instead
+    // of 1.06x of the unpipelined loop).  Measured against that loop (S^T,
     // softmax and PV one after the other, tiles staged through registers):
     // 4096 x 32 heads 142 -> 134 us, 16384 x 64 heads 4069 -> 3827 us (1081
     // -> 1149 TFLOP/s, 3105 cycles per tile instead of about 3900 at a clock
@@ -619,24 +622,24 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
     ReadAddr<D> ra;
     cp.init(wave, lane);
     ra.init(lane);
-    const uint32_t lk = lds_address(smem), lv = lk + 4 * kT;
+    const uint32_t lk = lds_address(smem), lv = lk + R * kT;
     const char* sk = smem;
-    const char* sv = smem + 4 * kT;
+    const char* sv = smem + R * kT;
     constexpr int kC = TileCopy<D, NW>::kPer;     // copies per tile and tensor
-    // Every group has at least 4 tiles (its 256 queries).  The compiler waits
-    // for Q with nothing left in flight, so only what the first steps need is
-    // issued before Q's first use.
+    // The compiler waits for Q with nothing left in flight, so only what the
+    // first steps need is issued before Q's first use.
     cp.k(bk, 0, lk, wave);
     cp.v(bv, 0, lv, wave);
-    cp.k(bk, 1, lk + kT, wave);
+    if (ntiles > 1) cp.k(bk, 1, lk + kT, wave);
 #pragma unroll
     for (int cc = 0; cc < G::kDChunks; ++cc) asm volatile("" : "+v"(w.qf[cc]));
     wait_copies<0>();
     __syncthreads();
-    cp.v(bv, 1, lv + kT, wave);
-    cp.k(bk, 2, lk + 2 * kT, wave);
-    cp.v(bv, 2, lv + 2 * kT, wave);
-    cp.k(bk, 3, lk + 3 * kT, wave);
+#pragma unroll
+    for (int u = 1; u < R - 1; ++u) {
+      if (u < ntiles) cp.v(bv, u, lv + u * kT, wave);
+      if (u + 1 < ntiles) cp.k(bk, u + 1, lk + (u + 1) * kT, wave);
+    }
     const int ntw = q0 / kKeyTile + 1;            // this wave's tiles; the last holds its diagonal
     f32x16_t s0[2], s1[2];
     float mx = 0.f;
@@ -647,53 +650,66 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
     };
     w.template step<2, true, false, kParts>(sk, sv, ra, lane, c, s1, s0, mx, [](auto, int) {},
                                             [&](f32x16_t sn[2]) { if (ntw == 1) mask_last(sn); });
-    __syncthreads();                              // K(0) read by every wave: K(4) may take its place
+    __syncthreads();                              // K(0) read by every wave: K(R) may take its place
     // End of step it: K(it+2) and V(it+1) have landed for every wave.  Copies
     // land in order; those issued after them may stay in flight.
     auto advance = [&](int it) {
-      if (it + 4 < ntiles) wait_copies<4 * kC>();
-      else if (it + 4 == ntiles) wait_copies<3 * kC>();
-      else if (it + 3 == ntiles) wait_copies<kC>();
-      else wait_copies<0>();
+      if constexpr (R == 4) {
+        if (it + 4 < ntiles) wait_copies<4 * kC>();
+        else if (it + 4 == ntiles) wait_copies<3 * kC>();
+        else if (it + 3 == ntiles) wait_copies<kC>();
+        else wait_copies<0>();
+      } else {
+        wait_copies<0>();
+      }
       __syncthreads();
     };
-    // Step it reads K(it+1) and V(it); V(it+3) and K(it+4) go where V(it-1) and
-    // K(it) were, last read in the step before.  b = it & 3.
+    // Step it reads K(it+1) and V(it); V(it+R-1) and K(it+R) go where V(it-1)
+    // and K(it) were, last read in the step before.  b = it % R.
     auto copy = [&](int it, int b, int i) {
       if (i < kC) {
-        if (it + 3 < ntiles) cp.v1(bv, it + 3, lv + ((b + 3) & 3) * kT, wave, i);
+        if (it + R - 1 < ntiles) cp.v1(bv, it + R - 1, lv + ((b + R - 1) % R) * kT, wave, i);
       } else {
-        if (it + 4 < ntiles) cp.k1(bk, it + 4, lk + b * kT, wave, i - kC);
+        if (it + R < ntiles) cp.k1(bk, it + R, lk + b * kT, wave, i - kC);
       }
     };
     auto fused = [&](int it, int b, f32x16_t sc[2], f32x16_t sn[2]) {
       w.template step<2, true, true, kParts>(
-          sk + ((b + 1) & 3) * kT, sv + b * kT, ra, lane, c, sc, sn, mx,
-          [&](auto, int j) {
-            if (j >= 2 && (j - 2) % 4 == 0 && (j - 2) / 4 < 2 * kC) copy(it, b, (j - 2) / 4);
+          sk + ((b + 1) % R) * kT, sv + b * kT, ra, lane, c, sc, sn, mx,
+          [&](auto n, int j) {
+            // from the third slot on, over the first five eighths of the step
+            constexpr int kGap = std::max(1, (decltype(n)::value * 5 / 8 - 2) / (2 * kC));
+            if (j >= 2 && (j - 2) % kGap == 0 && (j - 2) / kGap < 2 * kC) copy(it, b, (j - 2) / kGap);
           },
           [&](f32x16_t x[2]) { if (it + 2 == ntw) mask_last(x); });
       put_mass(it);
       advance(it);
     };
     int it = 0;
-    for (; it + 4 < ntw; it += 4) {
-      fused(it, 0, s0, s1);
-      fused(it + 1, 1, s1, s0);
-      fused(it + 2, 2, s0, s1);
-      fused(it + 3, 3, s1, s0);
+    if constexpr (R == 4) {
+      for (; it + 4 < ntw; it += 4) {
+        fused(it, 0, s0, s1);
+        fused(it + 1, 1, s1, s0);
+        fused(it + 2, 2, s0, s1);
+        fused(it + 3, 3, s1, s0);
+      }
+    } else {
+      for (; it + 2 < ntw; it += 2) {
+        fused(it, 0, s0, s1);
+        fused(it + 1, 1, s1, s0);
+      }
     }
     for (; it + 1 < ntw; ++it) {
-      fused(it, it & 3, s0, s1);
+      fused(it, it % R, s0, s1);
       s0[0] = s1[0];
       s0[1] = s1[1];
     }
     auto copies = [&](int it) {
 #pragma unroll
-      for (int i = 0; i < 2 * kC; ++i) copy(it, it & 3, i);
+      for (int i = 0; i < 2 * kC; ++i) copy(it, it % R, i);
     };
     copies(it);
-    w.template step<2, false, true, kParts>(sk, sv + (it & 3) * kT, ra, lane, c, s0, s1, mx,
+    w.template step<2, false, true, kParts>(sk, sv + (it % R) * kT, ra, lane, c, s0, s1, mx,
                                             [](auto, int) {}, [](f32x16_t*) {});
     put_mass(it);
     advance(it);

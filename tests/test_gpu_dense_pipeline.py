@@ -1,6 +1,6 @@
-"""The software-pipelined dense group (head_dim 128, 256 queries, rings of four
-key-value tiles): the shortest group, lengths around the ring's and the
-unrolled loop's wrap, and repeated passes, against the oracle."""
+"""The software-pipelined dense groups (256 queries at head_dim 128, else 128;
+rings of four or two key-value tiles): the shortest group, lengths around the
+ring's and the unrolled loop's wrap, and repeated passes, against the oracle."""
 
 import numpy as np
 import pytest
@@ -12,16 +12,19 @@ from parity_util import ACC_TOL, assert_attn, assert_lse, f64
 pytestmark = pytest.mark.gpu
 
 
-# 4, 8, 12 and 20 tiles in the last group: waves with 1 to 20 tiles, so every
-# remainder of the unrolled loop and every state of the rings occurs.
-@pytest.mark.parametrize("n,B,heads,kv_heads", [(256, 64, 1, 1), (512, 16, 2, 1), (768, 128, 3, 3),
-                                                (1280, 32, 4, 2)])
-def test_pipelined_dense_group(gpu_lib, n, B, heads, kv_heads):
+# Waves with 1 to 20 tiles, so every remainder of the unrolled loop and every
+# state of the rings occurs; d 128 lengths that 256 does not divide run 4-wave
+# groups.
+@pytest.mark.parametrize("n,B,heads,kv_heads,d", [
+    (256, 64, 1, 1, 128), (512, 16, 2, 1, 128), (768, 128, 3, 3, 128), (1280, 32, 4, 2, 128),
+    (128, 16, 1, 1, 128), (640, 128, 2, 2, 128), (128, 64, 2, 1, 64), (384, 32, 3, 3, 64),
+    (1152, 128, 2, 1, 64), (128, 32, 1, 1, 96), (256, 128, 2, 2, 96), (896, 16, 2, 1, 96)])
+def test_pipelined_dense_group(gpu_lib, n, B, heads, kv_heads, d):
     w = gpu_lib
-    g = torch.Generator().manual_seed(n + B)
-    q = (torch.randn((1, heads, n, 128), generator=g) * 2).to(torch.bfloat16)
-    k, v = (torch.randn((1, kv_heads, n, 128), generator=g).to(torch.bfloat16) for _ in range(2))
-    s = w.make_shape(1, heads, n, 128, B, kv_heads=kv_heads)
+    g = torch.Generator().manual_seed(n + B + d)
+    q = (torch.randn((1, heads, n, d), generator=g) * 2).to(torch.bfloat16)
+    k, v = (torch.randn((1, kv_heads, n, d), generator=g).to(torch.bfloat16) for _ in range(2))
+    s = w.make_shape(1, heads, n, d, B, kv_heads=kv_heads)
     qd, kd, vd, ws = q.cuda(), k.cuda(), v.cuda(), w.mass_workspace(s)
     first = None
     for _ in range(4):     # the same bits every time: no pass reads a tile before it landed
@@ -36,7 +39,7 @@ def test_pipelined_dense_group(gpu_lib, n, B, heads, kv_heads):
         assert all(torch.equal(a, b) for a, b in zip(first, (o, lse, acc, plain)))
     qe, ke, ve = f64(q), O.expand_kv(f64(k), heads), O.expand_kv(f64(v), heads)
     o_ref, l_ref = O.dense_attention(qe, ke, ve)
-    assert_attn(first[0], o_ref, f"n={n} B={B}")
+    assert_attn(first[0], o_ref, f"n={n} B={B} d={d}")
     assert_attn(first[3], o_ref, "without masses")     # its row sums run in another order
     assert_lse(first[1], l_ref)
     assert np.abs(f64(first[2]) - O.block_mass(qe, ke, B)).max() <= ACC_TOL
