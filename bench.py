@@ -284,7 +284,7 @@ def measure(cfg, K, W, tau=None, mode="accumulate", diag=False, steps=None, matc
     res = dict(
         workload=cfg.name, mode=mode, tau=float(tau if tau is not None else cfg.tau),
         late_kernel=("sparse_group_kernel" if pipe.grouped else
-                     "sparse_row16_kernel" if cfg.block == 16 else "sparse_attn_kernel"),
+                     f"sparse_row{cfg.block}_kernel" if cfg.block < 64 else "sparse_attn_kernel"),
         shape=f"batch {cfg.batch}, {cfg.heads} heads" + (f" over {cfg.kvh} kv heads" if cfg.grouped else "")
               + f", d {cfg.head_dim}, seq {cfg.seq_len}, block {cfg.block}, {cfg.discovery_steps} discovery "
               f"+ {cfg.late_steps} late steps",

@@ -794,6 +794,29 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
 }
 
 // ---------------------------------------------------------------------------
+// A support row's valid ids (0..qb) in order, 64 read at a time; ids outside
+// are skipped.  Everything but `ids` is wave-uniform.
+// ---------------------------------------------------------------------------
+struct RowIds {
+  const int32_t* col_idx;
+  int e, end, qb, ids;
+  uint64_t left;
+  __device__ __forceinline__ RowIds(const int32_t* row_ptr, const int32_t* ci, int row, int qb_)
+      : col_idx(ci), e(row_ptr[row]), end(row_ptr[row + 1]), qb(qb_), ids(0), left(0) {}
+  __device__ __forceinline__ int next(int lane) {    // -1: no more
+    while (left == 0) {
+      if (e >= end) return -1;
+      ids = e + lane < end ? col_idx[e + lane] : -1;
+      left = __builtin_amdgcn_ballot_w64((unsigned)ids <= (unsigned)qb);
+      e += 64;
+    }
+    const int at = __builtin_ctzll(left);
+    left &= left - 1;
+    return (int)__builtin_amdgcn_readlane(ids, at);
+  }
+};
+
+// ---------------------------------------------------------------------------
 // Block-sparse attention over a CSR support.  One work-group per (batch,
 // head, query block) row of 64- or 128-key blocks, NW = block/32 waves, in
 // tiles of 64 keys.
@@ -801,76 +824,124 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
 // wise_select_support writes the rows of each head together, longest support
 // first, so an XCD works through a few heads at a time and their K/V tiles
 // stay in its L2.
+//
+// Bound by the round trip of a tile to L2 and beyond: what counts is groups
+// per CU and how long their copies have to land.  K and V are copied straight
+// into LDS, one tile each without row pads (32 KB at d 128), the next K after
+// S^T and the next V after PV, each with half a tile of work to land; with no
+// tile in registers d 128 takes 191 VGPRs instead of 255 and five groups fit
+// the LDS of a CU instead of four (three waves per SIMD at d 64 and 96; at d
+// 128 they would spill 42 VGPRs).  Four barriers per tile, of two or four waves,
+// cost less than that gives.  Against tiles staged through registers:
+// 64-key blocks 4096 x 32 heads of 128 at density 0.43 95.9 -> 88.0 us, 110
+// heads of 96 at 0.52 284 -> 252, 128 grouped heads of 64 at 0.56 220 -> 210;
+// 128-key blocks 4096 x 32 heads of 128 at 0.65 108.6 -> 102.0.  Same bits.
 // ---------------------------------------------------------------------------
 template <int D, int NW>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3)))
 sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
                    const uint16_t* __restrict__ V, const int32_t* __restrict__ row_ptr,
                    const int32_t* __restrict__ col_idx, const int32_t* __restrict__ order,
                    uint16_t* __restrict__ O, float* __restrict__ lse, int n, int nb, int rows,
                    int heads, int gq, Sched sc, float c) {
   using G = Geo<D>;
-  constexpr int kNT = NW * 64, kB = NW * 32, kTPB = kB / kKeyTile;
-  static_assert(kTPB >= 1 && kB % kKeyTile == 0, "block / key tile");
-  __shared__ __attribute__((aligned(16))) uint16_t ks[G::kKElems];
-  __shared__ __attribute__((aligned(16))) uint16_t vt[G::kVElems];
+  constexpr int kB = NW * 32, kTPB = kB / kKeyTile;
+  constexpr int kRow = Swizzle<D>::kRow, kTile = Swizzle<D>::kTile;   // bytes
+  constexpr int kP = D / 32;                        // 1 KB copies per 16 rows
+  constexpr int kU = 4 / NW, kC = kU * kP;          // a wave's 16-row pieces and copies of a tile
+  static_assert(kTPB >= 1 && kB % kKeyTile == 0 && 4 % NW == 0, "block / key tile");
+  __shared__ __attribute__((aligned(1024))) char kt[kTile], vt[kTile];
   int sh, sit;
   if (!sched_slot(sc, sh, sit)) return;
   const int row = order ? order[sh * nb + sit] : sh * nb + (nb - 1 - sit);
   if ((unsigned)row >= (unsigned)rows) return;
   const int bh = row / nb, qb = row % nb;
   const size_t hoff = (size_t)bh * n * D;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q0 = qb * kB + 32 * wave;
-  const int beg = row_ptr[row];
-  int nent = row_ptr[row + 1] - beg;
-  // Ids past the diagonal form a suffix of the ascending row: dropping them
-  // leaves the diagonal block, when present, as the last entry, the one the
-  // masked tail below handles.
-  while (nent > 0 && col_idx[beg + nent - 1] > qb) --nent;
   const size_t kvoff = (size_t)kv_head(bh, heads, gq) * n * D;
-  const __amdgpu_buffer_rsrc_t rk = buffer_rsrc(K + kvoff), rv = buffer_rsrc(V + kvoff);
-
-  // Tile it of the row: entry it / kTPB, sub-tile it % kTPB.  Ids outside
-  // 0..qb are skipped (their tile is never loaded out of bounds nor used).
-  auto tile_key = [&](int it, bool& ok) {
-    const int kb = col_idx[beg + it / kTPB];
-    ok = (unsigned)kb <= (unsigned)qb;
-    return ok ? kb * kB + (it % kTPB) * kKeyTile : 0;
-  };
+  const u32x4_t bk = buffer_words(K + kvoff), bv = buffer_words(V + kvoff);
+  const uint32_t lk = lds_address(kt), lv = lds_address(vt);
+  RowIds ids(row_ptr, col_idx, row, qb);
 
   WaveRows<D> w;
   w.load_q(Q + hoff, q0, lane);
   w.reset();
-  TileStage<D, kNT> st;
-  const int ntiles = nent * kTPB;
-  // Entries are ascending, so only the last one can be the diagonal block:
-  // every earlier tile lies wholly below this group's queries.
-  const int nfull = (nent - 1) * kTPB;
-  bool ok = false;
-  int key0 = ntiles > 0 ? tile_key(0, ok) : 0;
-  if (ntiles > 0) st.load(rk, rv, key0, tid);
-  for (int it = 0; it < nfull; ++it) {
-    st.store(ks, vt, tid);
-    __syncthreads();
-    bool ok_next;
-    const int key_next = tile_key(it + 1, ok_next);
-    st.load(rk, rv, key_next, tid);
-    if (ok && key0 + kKeyTile - 1 < qb * kB) w.template attend<false>(ks, vt, lane, c, key0, q0);
-    __syncthreads();
-    key0 = key_next;
-    ok = ok_next;
+  ReadAddr<D> ra;
+  ra.init(lane);
+  uint32_t ko[kP], vo[kP];                          // source bytes of this lane's copies in 16 rows
+#pragma unroll
+  for (int i = 0; i < kP; ++i) {
+    const int at = 1024 * i + 16 * lane, r = at / kRow, ch = at % kRow / 16;
+    ko[i] = k_lds_row(r) * kRow + Swizzle<D>::k_chunk(r, ch) * 16;
+    vo[i] = r * kRow + (Swizzle<D>::v_block(r, ch >> 2) * 4 + (ch & 3)) * 16;
   }
-  for (int it = max(nfull, 0); it < ntiles; ++it) {
-    st.store(ks, vt, tid);
+  auto copy = [&](u32x4_t r, const uint32_t off[kP], int key0, uint32_t lds) {
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+#pragma unroll
+      for (int i = 0; i < kP; ++i) {
+        const int at = wave * kU + u;
+        copy16_to_lds(r, off[i], (uint32_t)(key0 + 16 * at) * kRow, lds + 1024 * (at * kP + i));
+      }
+  };
+  // The row's 64-key tiles: the first key of the next one, -1 past the last.
+  int blk = -1, sub = kTPB - 1;
+  auto next_key = [&] {
+    if (sub + 1 < kTPB) {
+      ++sub;
+    } else {
+      blk = ids.next(lane);
+      sub = 0;
+    }
+    return blk < 0 ? -1 : blk * kB + sub * kKeyTile;
+  };
+  int key0 = next_key();
+#pragma unroll
+  for (int i = 0; i < G::kDChunks; ++i) asm volatile("" : "+v"(w.qf[i]));   // Q has landed: only copies count below
+  if (key0 >= 0) {
+    copy(bk, ko, key0, lk);
+    copy(bv, vo, key0, lv);
+  }
+  while (key0 >= 0) {
+    const int next = next_key();
+    const bool mine = key0 <= q0;                   // else the tile lies past this wave's queries
+    wait_copies<kC>();                              // this tile's K; its V may be in flight
     __syncthreads();
-    bool ok_next = false;
-    const int key_next = (it + 1 < ntiles) ? tile_key(it + 1, ok_next) : 0;
-    if (it + 1 < ntiles) st.load(rk, rv, key_next, tid);
-    if (ok && key0 <= q0) w.template attend<true>(ks, vt, lane, c, key0, q0);
+    f32x16_t s[2] = {f32x16_t{}, f32x16_t{}};
+    if (mine) {
+#pragma unroll
+      for (int i = 0; i < G::kDChunks; ++i)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          s[t] = mfma32x32x16(*(const u32x4_t*)(kt + ra.k[i] + 32 * t * kRow), w.qf[i], s[t]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();                                // K read: its place is free
+    if (next >= 0) copy(bk, ko, next, lk);
+    u32x4_t pb[4];
+    if (mine) {
+      if (key0 + kKeyTile - 1 > q0) WaveRows<D>::template mask<2>(s, key0, q0 + (lane & 31), lane);
+      w.template softmax<2>(s, pb, c);
+    }
+    if (next >= 0) wait_copies<kC>();               // this tile's V; the next K may be in flight
+    else wait_copies<0>();
     __syncthreads();
-    key0 = key_next;
-    ok = ok_next;
+    if (mine) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int t = 0; t < G::kDTiles; ++t) {
+          const char* p = vt + ra.v[t] + 16 * ks * kRow;
+          const u32x2_t lo = lds_read_tr16((const uint16_t*)p);
+          const u32x2_t hi = lds_read_tr16((const uint16_t*)(p + 4 * kRow));
+          w.o[t] = mfma32x32x16(u32x4_t{lo[0], lo[1], hi[0], hi[1]}, pb[ks], w.o[t]);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();                                // V read: its place is free
+    if (next >= 0) copy(bv, vo, next, lv);
+    key0 = next;
   }
   w.finish(O + hoff, lse ? lse + (size_t)bh * n : nullptr, q0, lane);
 }
@@ -1040,29 +1111,6 @@ sparse_group_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
   }
   w.finish(O + hoff, lse ? lse + (size_t)bh * n : nullptr, q0, lane);
 }
-
-// ---------------------------------------------------------------------------
-// A support row's valid ids (0..qb) in order, 64 read at a time; ids outside
-// are skipped.  Everything but `ids` is wave-uniform.
-// ---------------------------------------------------------------------------
-struct RowIds {
-  const int32_t* col_idx;
-  int e, end, qb, ids;
-  uint64_t left;
-  __device__ __forceinline__ RowIds(const int32_t* row_ptr, const int32_t* ci, int row, int qb_)
-      : col_idx(ci), e(row_ptr[row]), end(row_ptr[row + 1]), qb(qb_), ids(0), left(0) {}
-  __device__ __forceinline__ int next(int lane) {    // -1: no more
-    while (left == 0) {
-      if (e >= end) return -1;
-      ids = e + lane < end ? col_idx[e + lane] : -1;
-      left = __builtin_amdgcn_ballot_w64((unsigned)ids <= (unsigned)qb);
-      e += 64;
-    }
-    const int at = __builtin_ctzll(left);
-    left &= left - 1;
-    return (int)__builtin_amdgcn_readlane(ids, at);
-  }
-};
 
 // ---------------------------------------------------------------------------
 // Block-sparse attention for 32-key blocks: one one-wave work-group per

@@ -51,17 +51,19 @@ class WisePipeline:
     # union of consecutive rows' supports grows as the density falls, and the
     # break-even is where it costs what the shared staging saves.  Late step,
     # grouped over one-row time on the same supports:
-    #   block 64, 4 rows, d 128: 1.36 at density 0.39, 1.18 at 0.58, 1.08 at
-    #     0.69, 1.04 at 0.74, 0.95 at 0.80, 0.94 at 0.88, 0.88 at 0.91
-    #   block 64, 2 rows, d 128 (lengths 256 does not divide): 1.05 at 0.80,
-    #     about 1.03 at 0.91
-    #   block 64, 2 rows, d 96: 1.01 at 0.30, 0.98 at 0.42 and 0.54, 1.00 at
-    #     0.55, 0.97 at 0.66, 0.94 at 0.78, 0.90 at 0.89-0.95
-    #   block 64, 2 rows, d 64: 1.07 at 0.23, 1.02 at 0.58, 0.92 at 0.89
-    #   block 128, 2 rows, d 128: 1.01 at 0.70, 1.00 at 0.80, 0.97 at 0.91,
-    #     0.97 at 0.96
-    GROUP_DENSITY = {(64, 4, 128): 0.78, (64, 2, 128): None, (64, 2, 96): 0.40,
-                     (64, 2, 64): 0.70, (128, 2, 128): 0.80}
+    #   block 64, 4 rows, d 128: 1.35 at density 0.43, 1.14 at 0.67, 1.03 at
+    #     0.79; 0.95 at 0.90 and 0.93 at 0.95 (8192 and 16384 tokens), 0.98 to
+    #     1.01 at 0.91 (4096), 1.03 at 0.89 (2048)
+    #   block 64, 2 rows, d 128 (lengths 256 does not divide): 1.18 at 0.54,
+    #     0.98 at 1.00
+    #   block 64, 2 rows, d 96: 1.14 at 0.52, 1.03 at 0.79, 1.02 at 0.91, 0.99
+    #     at 0.96, 0.98 at 1.00
+    #   block 64, 2 rows, d 64: 1.09 at 0.23, 1.06 at 0.56, 1.02 at 0.72, 0.99
+    #     at 0.80, 0.92 to 0.96 at 0.92 and 0.96
+    #   block 128, 2 rows, d 128: 1.16 at 0.65, 1.05 at 0.80, 1.03 at 0.91,
+    #     1.02 at 0.96, 1.00 at 1.00
+    GROUP_DENSITY = {(64, 4, 128): 0.86, (64, 2, 128): None, (64, 2, 96): 0.95,
+                     (64, 2, 64): 0.77, (128, 2, 128): None}
 
     def __init__(self, batch, heads, seq_len, head_dim, block, tau, flags=wise.WISE_DEFAULT_FLAGS,
                  scale=0.0, device="cuda", mode="accumulate", window=4, kv_heads=0,
