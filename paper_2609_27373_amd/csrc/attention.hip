@@ -1422,7 +1422,18 @@ static hipError_t launch_dense_d(const Dims& s, const void* q, const void* k, co
   // Queries per group (dense_query_tile): 256 for d 128 (each staged K/V tile
   // then feeds twice the MFMA work; 6-8% faster at 4K-32K, slower at d 64
   // and 96), else 128 when they divide n (always so for 128-key blocks).
-  const int qt = dense_query_tile(s);
+  //
+  // A grid of 8-wave groups that leaves CUs without a second group lasts as
+  // long as its longest group, whose two waves per SIMD take turns at the
+  // matrix cores: groups of 4 waves walk the same tiles with one.  256 CUs;
+  // dense time in groups of 256 and of 128 queries, by the former's count: 16
+  // (4096 x 1 head) 92 / 68 us, 64 (16384 x 1) 336 / 247, 128 (2048 x 16) 53.9
+  // / 40.8, 192 (4096 x 12) 96.9 / 82.9, 256 (8192 x 8) 192 / 174, 320 (4096 x
+  // 20) 110.9 / 104.2, 384 (8192 x 12) 223 / 217, 512 (16384 x 8) 500 / 504;
+  // with 64-key masses 320: 116.7 / 114.1, 384: 122.1 / 124.9.  The same bits;
+  // the mass workspace of 256-query tiles is the larger one.
+  int qt = dense_query_tile(s);
+  if (qt == 256 && (int64_t)s.bh * (s.n / 256) <= 320) qt = 128;
   if constexpr (D == 128) {
     if (qt == 256) {
       launch_dense_bm<D, 8>(s, Q, K, V, (uint16_t*)o, lse, acc, ws, st);
@@ -1449,8 +1460,9 @@ int dense_query_tile(const Dims& s) {
 }
 
 size_t mass_workspace_bytes(const Dims& s) {
-  // Matches dense_attn_kernel: tiles of T = dense_query_tile queries,
-  // entries of E keys, tile qt holding (qt+1)*T/E entries of T queries.
+  // Enough for dense_attn_kernel: tiles of T = dense_query_tile queries (fewer
+  // need less), entries of E keys, tile qt holding (qt+1)*T/E entries of T
+  // queries.
   const size_t e = s.block < 64 ? s.block : 64;
   const size_t qt = (size_t)dense_query_tile(s);
   const size_t nq = s.n / qt;

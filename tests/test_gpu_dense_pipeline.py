@@ -43,3 +43,25 @@ def test_pipelined_dense_group(gpu_lib, n, B, heads, kv_heads, d):
     assert_attn(first[3], o_ref, "without masses")     # its row sums run in another order
     assert_lse(first[1], l_ref)
     assert np.abs(f64(first[2]) - O.block_mass(qe, ke, B)).max() <= ACC_TOL
+
+
+@pytest.mark.parametrize("n,B,few,many", [(512, 64, 1, 161), (768, 128, 106, 107), (1024, 16, 3, 81), (1280, 32, 64, 65)])
+def test_small_grid_gives_the_same_bits(gpu_lib, n, B, few, many):
+    """head_dim 128: 320 groups of 256 queries at most run as groups of 128,
+    more as they are; a head's outputs do not depend on it."""
+    w = gpu_lib
+    assert few * n <= 320 * 256 < many * n
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, k, v = (torch.randn((1, many, n, 128), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    out = []
+    for h in (few, many):
+        s = w.make_shape(1, h, n, 128, B)
+        qh, kh, vh = (x[:, :h].contiguous() for x in (q, k, v))
+        o, lse = torch.empty_like(qh), torch.empty((1, h, n), device="cuda")
+        acc = torch.zeros((1, h, n // B, n // B), device="cuda")
+        plain = torch.empty_like(qh)
+        w.wise_dense_attn_accum(s, qh, kh, vh, o, lse, acc, w.mass_workspace(s))
+        w.wise_dense_attn_accum(s, qh, kh, vh, plain, None, None)
+        torch.cuda.synchronize()
+        out.append([x[:, :few] for x in (o, lse, acc, plain)])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
