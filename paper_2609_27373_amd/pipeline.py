@@ -22,7 +22,8 @@ Two late-step kernels compute the same outputs (late_kernel):
              density (nnz over the causal block pairs) is at least
              group_density (by default the measured break-even of the
              library's group shape and head_dim, GROUP_DENSITY; some shapes
-             never), rows otherwise.  The
+             and grids too small to fill the chip, GROUP_QUERIES, never),
+             rows otherwise.  The
              first select() reads nnz back (one synchronisation); later ones
              copy it to pinned host memory asynchronously, and the choice
              follows when the copy has landed (checked without waiting at
@@ -64,6 +65,14 @@ class WisePipeline:
     #     1.02 at 0.96, 1.00 at 1.00
     GROUP_DENSITY = {(64, 4, 128): 0.86, (64, 2, 128): None, (64, 2, 96): 0.95,
                      (64, 2, 64): 0.77, (128, 2, 128): None}
+    # Queries (over batch and heads) up to which "auto" stays with one row per
+    # work-group: groups of rows then leave CUs idle and the longest decides.
+    # Full supports of 64-key blocks, grouped / one-row us by queries / 256:
+    # d 128: 16 (1024 x 4 heads) 34.7 / 25.1, 128 (16384 x 2) 420 / 323, 256
+    # (4096 x 16) 116.9 / 103.6, 384 (4096 x 24) 127.3 / 129.5; d 96: 128 (4096
+    # x 8) 76.0 / 74.1, 256 (4096 x 16) 85.0 / 84.3, 384 102.4 / 108.1; d 64: 128
+    # 64.6 / 63.7, 256 70.4 / 68.3, 384 79.9 / 83.8
+    GROUP_QUERIES = 320 * 256
 
     def __init__(self, batch, heads, seq_len, head_dim, block, tau, flags=wise.WISE_DEFAULT_FLAGS,
                  scale=0.0, device="cuda", mode="accumulate", window=4, kv_heads=0,
@@ -92,7 +101,8 @@ class WisePipeline:
         self.late_kernel = late_kernel
         group_rows = wise.wise_sparse_group_rows(self.shape)
         if group_density is None:
-            group_density = self.GROUP_DENSITY.get((block, group_rows, head_dim))
+            group_density = (self.GROUP_DENSITY.get((block, group_rows, head_dim))
+                             if batch * heads * seq_len > self.GROUP_QUERIES else None)
         self.group_density = None if group_density is None else float(group_density)
         self.grouped = late_kernel == "grouped"
         self._auto = late_kernel == "auto" and group_rows > 0 and self.group_density is not None

@@ -178,6 +178,17 @@ def test_group_density_covers_every_group_shape(lib):
     assert seen == set(WisePipeline.GROUP_DENSITY)
 
 
+def test_group_density_small_grids(lib):
+    """Up to GROUP_QUERIES queries the default is "never"; a density that the
+    caller gives stays."""
+    from paper_2609_27373_amd.pipeline import WisePipeline
+    heads = WisePipeline.GROUP_QUERIES // 1024
+    make = lambda h, **kw: WisePipeline(1, h, 1024, 128, 64, 0.9, device="cpu", late_kernel="rows", **kw)  # noqa: E731
+    assert make(heads).group_density is None
+    assert make(heads + 1).group_density == WisePipeline.GROUP_DENSITY[(64, 4, 128)]
+    assert make(1, group_density=0.5).group_density == 0.5
+
+
 MIS8 = ctypes.c_void_p(4096 + 4)    # 4-byte but not 8-byte aligned
 
 
