@@ -40,8 +40,8 @@ namespace wise {
 // the S^T accumulator comes out in PV operand order; V rows in natural order).  Loads for the next tile are
 // issued before the current one is computed, so the memory latency hides
 // behind the MFMA work; stores go to an LDS tile no wave still reads: after
-// the barrier that retires it, or, in the 8-wave dense group, into its
-// second buffer.
+// the barrier that retires it, or, in the 8-wave grouped late step, into its
+// second buffer.  Used by that kernel's groups and the 2-wave dense group.
 // ---------------------------------------------------------------------------
 template <int D, int NT>
 struct TileStage {
@@ -951,7 +951,7 @@ sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
 
 // ---------------------------------------------------------------------------
 // Block-sparse attention over groups of consecutive rows of BR-key blocks:
-// the dense kernel's work-group (NW waves, 32 NW queries: 4 rows of 64 or 2
+// a work-group of the dense kernel's size (NW waves, 32 NW queries: 4 rows of 64 or 2
 // of 128 keys at head_dim 128, 2 rows of 64 otherwise) walks the ascending
 // union of its rows' supports in 64-key tiles, staging each tile once for all
 // its waves, and each wave attends only the tiles its own row holds (its
@@ -1073,7 +1073,7 @@ sparse_group_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
   bool have = next(kb, m0);
   if (have && kb != 0) st.load(rk, rv, kb * kKeyTile, tid);
   if constexpr (kBufs == 2) {
-    // Double-buffered as the dense 8-wave group: tile i+1 is stored into the
+    // Double-buffered (an 8-wave group fills its CU alone): tile i+1 is stored into the
     // idle buffer right after tile i is computed, one barrier per tile.
     if (have) {
       st.store(ks, vt, tid);
