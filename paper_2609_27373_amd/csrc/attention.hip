@@ -31,6 +31,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "csr_entries.hpp"
 #include "wise_device.hpp"
 #include "wise_kernels.hpp"
 namespace wise {
@@ -802,16 +803,17 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
 // ---------------------------------------------------------------------------
 struct RowIds {
   const int32_t* col_idx;
-  int e, end, qb, ids;
+  Entries e;
+  int qb, ids;
   uint64_t left;
   __device__ __forceinline__ RowIds(const int32_t* row_ptr, const int32_t* ci, int row, int qb_)
-      : col_idx(ci), e(row_ptr[row]), end(row_ptr[row + 1]), qb(qb_), ids(0), left(0) {}
+      : col_idx(ci), e(row_ptr[row], row_ptr[row + 1]), qb(qb_), ids(0), left(0) {}
   __device__ __forceinline__ int next(int lane) {    // -1: no more
     while (left == 0) {
-      if (e >= end) return -1;
-      ids = e + lane < end ? col_idx[e + lane] : -1;
+      if (!e.more()) return -1;
+      ids = e.holds(lane) ? col_idx[e.at + lane] : -1;
       left = __builtin_amdgcn_ballot_w64((unsigned)ids <= (unsigned)qb);
-      e += 64;
+      e.advance(64);
     }
     const int at = __builtin_ctzll(left);
     left &= left - 1;
@@ -1013,8 +1015,9 @@ sparse_group_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
   }
   __syncthreads();
   // Valid ids (0..qb) of every row of the group into the bitmasks.
-  for (int e = bound[0] + tid; e < bound[kR]; e += kNT) {
-    const int kb = col_idx[e];
+  for (Entries all(bound[0], bound[kR]); all.more(); all.advance(kNT)) {
+    if (!all.holds(tid)) break;
+    const int e = all.at + tid, kb = col_idx[e];
     int r = 0;
 #pragma unroll
     for (int j = 1; j < kR; ++j) r += e >= bound[j];

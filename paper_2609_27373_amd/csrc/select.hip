@@ -24,6 +24,7 @@
 // retained future full-attention mass).
 #include <mutex>
 
+#include "csr_entries.hpp"
 #include "wise.h"
 #include "wise_device.hpp"
 #include "wise_kernels.hpp"
@@ -728,8 +729,8 @@ row_mass_kernel(const float* __restrict__ r, const int32_t* __restrict__ row_ptr
   const float* v = r + (size_t)row * nb;
   double inside = 0.0, total = 0.0;
   for (int kb = lane; kb <= qb; kb += 64) total += (double)v[kb];
-  for (int e = row_ptr[row] + lane; e < row_ptr[row + 1]; e += 64) {
-    const int kb = col_idx[e];
+  for (Entries e(row_ptr[row], row_ptr[row + 1]); e.holds(lane); e.advance(64)) {
+    const int kb = col_idx[e.at + lane];
     if (kb >= 0 && kb <= qb) inside += (double)v[kb];
   }
 #pragma unroll
