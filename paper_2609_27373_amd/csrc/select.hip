@@ -497,13 +497,19 @@ static SelectWs select_ws(const Dims& s) {
 
 size_t select_workspace_bytes(const Dims& s) { return select_ws(s).total; }
 
+// HIP refuses a grid of 2^32 threads or more in one dimension.  The kernels of
+// a call read what the ones before them wrote (the CSR kernel writes col_idx
+// where the counts say), so a call launches all of its kernels or none.
+static bool grid_fits(int64_t groups, int threads) { return groups * threads < (int64_t)1 << 32; }
+
+static int64_t row_groups(const Dims& s) { return ((int64_t)s.bh * s.nb + kSelWaves - 1) / kSelWaves; }
+
 // Per-row selection of every row: counts (may be null) and bitmasks.
 static void launch_rows(const Dims& s, const float* acc, float tau, uint32_t flags,
                         int32_t* counts, uint64_t* masks, hipStream_t st) {
   const int rows = s.bh * s.nb, words = mask_words(s);
-  const int groups = (rows + kSelWaves - 1) / kSelWaves;
   const size_t smem = kSelWaves * select_row_lds(s.nb);
-  const dim3 sg(groups), sb(kSelWaves * 64);
+  const dim3 sg((unsigned)row_groups(s)), sb(kSelWaves * 64);
   const double dtau = (double)tau;
   if (s.nb <= 64)
     hipLaunchKernelGGL(select_rows_kernel<1>, sg, sb, smem, st, acc, rows, s.nb, dtau, flags, counts, masks, words);
@@ -523,6 +529,8 @@ static void launch_rows(const Dims& s, const float* acc, float tau, uint32_t fla
 constexpr int64_t kSumRows = 131072;
 constexpr int64_t kSumReads = (int64_t)1 << 28;
 
+static bool csr_fits(const Dims& s) { return grid_fits(s.bh, 1024); }
+
 static void launch_csr(const Dims& s, const int32_t* counts, const uint64_t* masks,
                        int32_t* row_ptr, int32_t* col_idx, int32_t* row_order, hipStream_t st) {
   const int rows = s.bh * s.nb, chunks = (s.nb + kCsrRows - 1) / kCsrRows;
@@ -541,6 +549,7 @@ static void launch_csr(const Dims& s, const int32_t* counts, const uint64_t* mas
 hipError_t launch_select(const Dims& s, const float* acc, float tau, uint32_t flags,
                          int32_t* row_ptr, int32_t* col_idx, int32_t* row_order, void* ws,
                          hipStream_t st) {
+  if (!grid_fits(row_groups(s), kSelWaves * 64) || !csr_fits(s)) return hipErrorInvalidConfiguration;
   const SelectWs w = select_ws(s);
   char* base = (char*)ws;
   auto* counts = (int32_t*)(base + w.counts);
@@ -637,15 +646,16 @@ union_rows_kernel(const uint64_t* __restrict__ masks, int n_masks, size_t slab, 
 hipError_t launch_support_from_masks(const Dims& s, const uint64_t* masks, int n_masks,
                                      uint32_t flags, int32_t* row_ptr, int32_t* col_idx,
                                      int32_t* row_order, void* ws, hipStream_t st) {
+  const int64_t groups = ((int64_t)s.bh * s.nb + kMaskThreads - 1) / kMaskThreads;
+  if (!grid_fits(groups, kMaskThreads) || !csr_fits(s)) return hipErrorInvalidConfiguration;
   const SelectWs w = select_ws(s);
   char* base = (char*)ws;
   auto* counts = (int32_t*)(base + w.counts);
   auto* umask = (uint64_t*)(base + w.masks);
   const int rows = s.bh * s.nb;
   const size_t slab = (size_t)rows * w.words;
-  hipLaunchKernelGGL(union_rows_kernel, dim3((rows + kMaskThreads - 1) / kMaskThreads),
-                     dim3(kMaskThreads), 0, st, masks, n_masks, slab, rows, s.nb, w.words, flags,
-                     counts, umask);
+  hipLaunchKernelGGL(union_rows_kernel, dim3((unsigned)groups), dim3(kMaskThreads), 0, st, masks,
+                     n_masks, slab, rows, s.nb, w.words, flags, counts, umask);
   launch_csr(s, counts, umask, row_ptr, col_idx, row_order, st);
   return hipGetLastError();
 }
@@ -765,8 +775,9 @@ hipError_t launch_support_mass(const Dims& s, const float* r, const int32_t* row
                                const int32_t* col_idx, double* row_mass, double* totals,
                                hipStream_t st) {
   const int rows = s.bh * s.nb;
-  hipLaunchKernelGGL(row_mass_kernel, dim3((rows + kSelWaves - 1) / kSelWaves),
-                     dim3(kSelWaves * 64), 0, st, r, row_ptr, col_idx, rows, s.nb, row_mass);
+  if (!grid_fits(row_groups(s), kSelWaves * 64)) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(row_mass_kernel, dim3((unsigned)row_groups(s)), dim3(kSelWaves * 64), 0, st,
+                     r, row_ptr, col_idx, rows, s.nb, row_mass);
   if (totals != nullptr)
     hipLaunchKernelGGL(mass_total_kernel, dim3(1), dim3(1024), 0, st, row_mass, rows, totals);
   return hipGetLastError();

@@ -1,0 +1,66 @@
+"""What the C calls launch, recorded under a stand-in for the HIP runtime
+(launch_recorder.c, no GPU): a call whose grids HIP would refuse launches
+nothing and says so."""
+
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2609_27373_amd import wise
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests")
+
+pytestmark = pytest.mark.skipif(shutil.which("gcc") is None, reason="no C compiler")
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    if not os.path.exists(wise.LIB_PATH):
+        from paper_2609_27373_amd import build
+        build.build()
+    exe = tmp_path_factory.mktemp("rec") / "recorder"
+    subprocess.run(["gcc", "-std=c99", "-Wall", "-Wextra", "-Werror", "-I", os.path.join(ROOT, "include"),
+                    os.path.join(HERE, "launch_recorder.c"), "-o", str(exe), wise.LIB_PATH,
+                    f"-Wl,-rpath,{os.path.dirname(wise.LIB_PATH)}"], check=True, capture_output=True, text=True)
+
+    def record(entry, batch, heads, n, d, block, option=1, kv_heads=1):
+        """([(verdict, kernel, grid x, y, z, threads)], status) of one call."""
+        line = f"{entry} {batch} {heads} {kv_heads} {n} {d} {block} {option}\n"
+        out = subprocess.run([str(exe)], input=line, capture_output=True, text=True, timeout=60, check=True).stdout.split("\n")
+        launches = []
+        for ln in out:
+            f = ln.split()
+            if f and f[0] in ("launch", "refused"):
+                launches.append((f[0], re.search(r"\d+([a-z]+(?:_[a-z0-9]+)*_kernel)", f[1]).group(1), *map(int, f[2:])))
+        return launches, int(out[-2].split()[1])
+
+    return record
+
+
+WISE_ERR_HIP = 6
+
+
+def test_recorder(recorder):
+    launches, status = recorder("dense", 1, 32, 4096, 128, 64, kv_heads=32)
+    assert status == 0 and launches == [("launch", "dense_attn_kernel", 512, 1, 1, 512)]
+
+
+# 2^26 rows: 64 threads each are more than a grid holds
+@pytest.mark.parametrize("entry", ["select", "step", "support"])
+@pytest.mark.parametrize("heads,nb", [(1 << 21, 32), (1 << 26, 1)])
+@pytest.mark.parametrize("order", [0, 1])
+def test_refused_rows_launch_nothing(recorder, entry, heads, nb, order):
+    launches, status = recorder(entry, 1, heads, 64 * nb, 64, 64, order)
+    assert status == WISE_ERR_HIP
+    assert all(verdict == "refused" for verdict, *_ in launches), launches
+
+
+@pytest.mark.parametrize("heads,nb", [(2147483647, 1), (1 << 30, 1)])
+def test_refused_union_launches_nothing(recorder, heads, nb):
+    launches, status = recorder("masks", 1, heads, 64 * nb, 64, 64)
+    assert status == WISE_ERR_HIP
+    assert all(verdict == "refused" for verdict, *_ in launches), launches
