@@ -22,6 +22,7 @@
 // "Stability of the Deployed Working Set") and the attention mass a support
 // retains from one step's block masses (Section 7.1 and Appendix B, the
 // retained future full-attention mass).
+#include <algorithm>
 #include <mutex>
 
 #include "csr_entries.hpp"
@@ -366,7 +367,8 @@ scan_kernel(const int32_t* __restrict__ counts, int rows, int32_t* __restrict__ 
 }
 
 // Counts and bitmasks -> row_ptr, col_idx and row order.  One group takes
-// kCsrRows rows of one head (grid: heads x chunks of a head):
+// kCsrRows rows of one head, or as many whole heads as kCsrRows rows hold at
+// most (per of the bh heads; grid: groups of heads x chunks of a head):
 //   its first entry   the sum of every earlier row's count (read again by each
 //                     group: at most kSumRows counts from L2), or row_ptr
 //                     where the scan has run
@@ -377,19 +379,24 @@ scan_kernel(const int32_t* __restrict__ counts, int rows, int32_t* __restrict__ 
 //                     lanes per row over the head's counts in LDS
 // Latency bound (6 us for 28160 rows, where a one-group scan, a scatter and an
 // order kernel took about 45); 16 waves per group put eight rows' masks of
-// each wave in flight at once.
+// each wave in flight at once.  Short heads share a group because a group's
+// own cost, 1024 threads and the sum before it, does not shrink with its rows:
+// CSR from masks, a group per head -> shared: 4096 heads of 8 blocks 29.1 ->
+// 9.1 us, 8192 of 16 151 -> 24.4 us (the three kernels: 39.9 and 135).
 constexpr int kCsrRows = 128;
 
 template <bool kScanned>
 __global__ void __launch_bounds__(1024)
-csr_kernel(const int32_t* __restrict__ counts, const uint64_t* __restrict__ masks, int nb, int words,
-           int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx, int32_t* __restrict__ order) {
-  __shared__ int head[1024];             // nb <= kMaxSelectBlocks
+csr_kernel(const int32_t* __restrict__ counts, const uint64_t* __restrict__ masks, int bh, int per,
+           int nb, int words, int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx,
+           int32_t* __restrict__ order) {
+  __shared__ int head[1024];             // counts of the group's heads: max(kCsrRows, nb) at most
   __shared__ int start[kCsrRows];
   __shared__ int wsum[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int base = blockIdx.x * nb;                        // the head's first row
-  const int r0 = blockIdx.y * kCsrRows, nr = min(kCsrRows, nb - r0);
+  const int h0 = blockIdx.x * per, base = h0 * nb;         // the group's first head and its first row
+  const int rows = min(per, bh - h0) * nb;                 // of its heads
+  const int r0 = blockIdx.y * kCsrRows, nr = min(kCsrRows, rows - r0);
   const int first = base + r0;
   // Up to eight rows' masks per wave, loaded before the sums they wait for.
   constexpr int kRowsPerWave = kCsrRows / 16;
@@ -399,7 +406,7 @@ csr_kernel(const int32_t* __restrict__ counts, const uint64_t* __restrict__ mask
     const int r = wave + 16 * i;
     m[i] = r < nr && lane < words ? masks[(size_t)(first + r) * words + lane] : 0ull;
   }
-  if (tid < nb) head[tid] = counts[base + tid];
+  if (tid < rows) head[tid] = counts[base + tid];
   int before = 0;
   if constexpr (!kScanned) {
     const int4* c4 = (const int4*)counts;                  // 256-byte aligned
@@ -434,7 +441,7 @@ csr_kernel(const int32_t* __restrict__ counts, const uint64_t* __restrict__ mask
     }
     if (wave == 1) {
       int low = head[r0 + lane];                           // rows 0 .. 63 of the chunk: nr > 64 or unused
-      if (r0 + lane >= nb) low = 0;
+      if (r0 + lane >= rows) low = 0;
 #pragma unroll
       for (int off = 32; off >= 1; off >>= 1) low += __shfl_xor(low, off, 64);
       inc += low;
@@ -461,17 +468,20 @@ csr_kernel(const int32_t* __restrict__ counts, const uint64_t* __restrict__ mask
     }
   }
   if (order != nullptr) {
-    const int r = tid >> 3, part = tid & 7;                // row of the chunk, eighth of the head
-    const int c = r < nr ? head[r0 + r] : 0;
+    const int r = r0 + (tid >> 3), part = tid & 7;         // row of the group's heads, eighth of its head
+    const bool live = (tid >> 3) < nr;
+    const int h = per > 1 ? r / nb * nb : 0;               // its head's first row
+    const int* own = head + h;
+    const int at = r - h, c = live ? own[at] : 0;
     int rank = 0;
-    if (r < nr)
+    if (live)
       for (int t = part; t < nb; t += 8) {
-        const int ct = head[t];
-        rank += (ct > c || (ct == c && t < r0 + r)) ? 1 : 0;
+        const int ct = own[t];
+        rank += (ct > c || (ct == c && t < at)) ? 1 : 0;
       }
 #pragma unroll
     for (int off = 4; off >= 1; off >>= 1) rank += __shfl_xor(rank, off, 64);
-    if (r < nr && part == 0) order[base + rank] = base + r0 + r;
+    if (live && part == 0) order[base + h + rank] = base + r;
   }
 }
 
@@ -529,19 +539,33 @@ static void launch_rows(const Dims& s, const float* acc, float tau, uint32_t fla
 constexpr int64_t kSumRows = 131072;
 constexpr int64_t kSumReads = (int64_t)1 << 28;
 
-static bool csr_fits(const Dims& s) { return grid_fits(s.bh, 1024); }
+// While the heads are fewer than the 1024-thread groups the chip holds, each
+// has a group of its own: its rows then share no wave.
+constexpr int kCsrGroups = 512;
+
+struct CsrGrid {
+  int per;                                              // heads per group
+  int64_t groups;                                       // x; the chunks of a head in y
+  int chunks;
+};
+static CsrGrid csr_grid(const Dims& s) {
+  const int fit = s.nb < kCsrRows ? kCsrRows / s.nb : 1;
+  const int per = (int)std::min<int64_t>(fit, ((int64_t)s.bh + kCsrGroups - 1) / kCsrGroups);
+  return {per, ((int64_t)s.bh + per - 1) / per, (s.nb + kCsrRows - 1) / kCsrRows};
+}
+static bool csr_fits(const Dims& s) { return grid_fits(csr_grid(s).groups, 1024); }
 
 static void launch_csr(const Dims& s, const int32_t* counts, const uint64_t* masks,
                        int32_t* row_ptr, int32_t* col_idx, int32_t* row_order, hipStream_t st) {
-  const int rows = s.bh * s.nb, chunks = (s.nb + kCsrRows - 1) / kCsrRows;
-  // x: heads (up to 2^31 - 1 groups), the chunks of a head in y
-  const dim3 grid(s.bh, chunks);
-  if (rows <= kSumRows && (int64_t)s.bh * chunks * rows / 2 <= kSumReads) {
-    hipLaunchKernelGGL(csr_kernel<false>, grid, dim3(1024), 0, st, counts, masks, s.nb,
+  const int rows = s.bh * s.nb;
+  const CsrGrid g = csr_grid(s);
+  const dim3 grid((unsigned)g.groups, g.chunks);
+  if (rows <= kSumRows && g.groups * g.chunks * rows / 2 <= kSumReads) {
+    hipLaunchKernelGGL(csr_kernel<false>, grid, dim3(1024), 0, st, counts, masks, s.bh, g.per, s.nb,
                        mask_words(s), row_ptr, col_idx, row_order);
   } else {
     hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, counts, rows, row_ptr);
-    hipLaunchKernelGGL(csr_kernel<true>, grid, dim3(1024), 0, st, counts, masks, s.nb,
+    hipLaunchKernelGGL(csr_kernel<true>, grid, dim3(1024), 0, st, counts, masks, s.bh, g.per, s.nb,
                        mask_words(s), row_ptr, col_idx, row_order);
   }
 }

@@ -52,9 +52,12 @@ def test_selection_paths(gpu_lib, kind, nb):
         assert np.array_equal(sched.row_order.cpu().numpy(), O.schedule_order(rp, nb))
 
 
-@pytest.mark.parametrize("heads,nb", [(8200, 16), (70, 3), (1, 1024)])
+# one head, several whole heads and part of a head per group of the CSR kernel; a last group that is not full
+@pytest.mark.parametrize("heads,nb", [(8200, 16), (70, 3), (1, 1024), (512, 1), (1300, 1), (1025, 2), (5000, 3), (1600, 42), (1600, 43), (600, 63),
+                                      (1030, 64), (520, 65), (2, 127), (2, 128), (2, 129), (70000, 2), (1 << 22, 1)])
 def test_csr_of_many_rows(gpu_lib, heads, nb):
-    """131200 rows (past the limit of the sums in the CSR kernel), row counts 4 does not divide."""
+    """131200 rows (past the limit of the sums in the CSR kernel), row counts 4 does not divide,
+    4194304 heads (a 1024-thread group for each would be more than a grid holds)."""
     w = gpu_lib
     rng = np.random.default_rng(heads)
     s = w.make_shape(1, heads, 64 * nb, 64, 64)

@@ -64,3 +64,22 @@ def test_refused_union_launches_nothing(recorder, heads, nb):
     launches, status = recorder("masks", 1, heads, 64 * nb, 64, 64)
     assert status == WISE_ERR_HIP
     assert all(verdict == "refused" for verdict, *_ in launches), launches
+
+
+# Up to 16777215 heads and 2^26 - 1 rows were accepted when each head's order had a 256-thread group.
+@pytest.mark.parametrize("heads,nb", [(1 << 22, 1), (6000000, 2), (16777215, 1), (16777215, 3), ((1 << 21) - 1, 32), (500000, 90), (1 << 17, 129)])
+@pytest.mark.parametrize("entry", ["select", "masks"])
+def test_many_heads_are_accepted(recorder, entry, heads, nb):
+    launches, status = recorder(entry, 1, heads, 64 * nb, 64, 64)
+    assert status == 0
+    assert all(verdict == "launch" for verdict, *_ in launches), launches
+
+
+@pytest.mark.parametrize("heads,nb", [(100000, 2), (8192, 16), (1000, 1), (512, 1), (513, 1), (1600, 42), (1600, 43), (2000, 64), (2000, 65), (9, 128),
+                                      (9, 129), (2, 1024)])
+def test_csr_groups_hold_whole_heads(recorder, heads, nb):
+    """128 rows of a head, or as many heads as 128 rows allow, once every head cannot have one of 512 groups."""
+    launches, _ = recorder("masks", 1, heads, 64 * nb, 64, 64)
+    (x, y), = [(f[2], f[3]) for f in launches if f[1] == "csr_kernel"]
+    per = min(max(1, 128 // nb), -(-heads // 512))
+    assert (x, y) == (-(-heads // per), -(-nb // 128))
