@@ -69,7 +69,7 @@ __device__ __forceinline__ u32x4_t buffer_words(const void* base) {
 // flight before each LDS read.
 __device__ __forceinline__ void copy16_to_lds(u32x4_t r, uint32_t voff, uint32_t soff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory");
+               :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory", "m0");
 }
 // At most N copies (or other vector memory operations) still in flight.
 template <int N>
