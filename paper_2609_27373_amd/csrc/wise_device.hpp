@@ -64,12 +64,12 @@ __device__ __forceinline__ u32x4_t buffer_words(const void* base) {
 }
 
 // 16 bytes per lane, global -> LDS without registers: lane l's bytes land at
-// LDS byte address lds + 16 l (lds wave-uniform).  The copy counts in vmcnt;
+// LDS byte address lds + 16 l (lds wave-uniform, in m0).  The copy counts in vmcnt;
 // issued as asm because the compiler would otherwise wait for every copy in
 // flight before each LDS read.
 __device__ __forceinline__ void copy16_to_lds(u32x4_t r, uint32_t voff, uint32_t soff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory", "m0");
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "{m0}"(lds), "v"(voff), "s"(r), "s"(soff) : "memory");
 }
 // At most N copies (or other vector memory operations) still in flight.
 template <int N>
