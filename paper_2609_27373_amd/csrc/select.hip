@@ -344,7 +344,7 @@ __device__ __forceinline__ int block_scan_1024(int x, int* wsum) {
 }
 
 // row_ptr[0] = 0, row_ptr[r+1] = counts[0] + ... + counts[r], by one group.
-// Only for row counts past kSumRows (see launch_csr).
+// Only where the csr groups would read too much (kSumReads).
 __global__ void __launch_bounds__(1024)
 scan_kernel(const int32_t* __restrict__ counts, int rows, int32_t* __restrict__ row_ptr) {
   __shared__ int wsum[16];
@@ -370,7 +370,7 @@ scan_kernel(const int32_t* __restrict__ counts, int rows, int32_t* __restrict__ 
 // kCsrRows rows of one head, or as many whole heads as kCsrRows rows hold at
 // most (per of the bh heads; grid: groups of heads x chunks of a head):
 //   its first entry   the sum of every earlier row's count (read again by each
-//                     group: at most kSumRows counts from L2), or row_ptr
+//                     group, from L2: kSumReads), or row_ptr
 //                     where the scan has run
 //   row_ptr           the scan of its own rows' counts from there
 //   col_idx           one wave per row at a time: set bits of the mask, ascending
@@ -534,10 +534,12 @@ static void launch_rows(const Dims& s, const float* acc, float tau, uint32_t fla
 }
 
 // counts + masks (in the workspace) -> row_ptr, col_idx, row_order.
-// Each csr group adds up the counts before its rows itself while every group
-// together reads little (groups x rows / 2 counts): one launch instead of two.
-constexpr int64_t kSumRows = 131072;
-constexpr int64_t kSumReads = (int64_t)1 << 28;
+// Each csr group adds up the counts before its rows itself while all groups
+// together read little, groups x rows / 2 counts from L2; past that one group
+// scans them first, 0.95 us per 1024 rows.  Both ways, CSR from masks: 131072
+// rows in 1024 groups (2^26 reads) 29 against 146 us, 1048576 in 8192 (2^32)
+// 553 against 1000, in 16256 groups of 129-block heads (2^33) 1071 against 1097.
+constexpr int64_t kSumReads = (int64_t)1 << 33;
 
 // While the heads are fewer than the 1024-thread groups the chip holds, each
 // has a group of its own: its rows then share no wave.
@@ -560,7 +562,7 @@ static void launch_csr(const Dims& s, const int32_t* counts, const uint64_t* mas
   const int rows = s.bh * s.nb;
   const CsrGrid g = csr_grid(s);
   const dim3 grid((unsigned)g.groups, g.chunks);
-  if (rows <= kSumRows && g.groups * g.chunks * rows / 2 <= kSumReads) {
+  if (g.groups * g.chunks * rows / 2 <= kSumReads) {
     hipLaunchKernelGGL(csr_kernel<false>, grid, dim3(1024), 0, st, counts, masks, s.bh, g.per, s.nb,
                        mask_words(s), row_ptr, col_idx, row_order);
   } else {

@@ -1,7 +1,7 @@
 """Selection where its paths meet: sums by digit against ranked rows (masses
 whose fp64 sums round, negative and infinite ones, ties at the cut, light
 masses few and many), chunk edges of the CSR kernel, and row counts past the
-one-launch limit.  Bit for bit the oracle's."""
+limit of its sums.  Bit for bit the oracle's."""
 
 import numpy as np
 import pytest
@@ -54,10 +54,10 @@ def test_selection_paths(gpu_lib, kind, nb):
 
 # one head, several whole heads and part of a head per group of the CSR kernel; a last group that is not full
 @pytest.mark.parametrize("heads,nb", [(8200, 16), (70, 3), (1, 1024), (512, 1), (1300, 1), (1025, 2), (5000, 3), (1600, 42), (1600, 43), (600, 63),
-                                      (1030, 64), (520, 65), (2, 127), (2, 128), (2, 129), (70000, 2), (1 << 22, 1)])
+                                      (1030, 64), (520, 65), (2, 127), (2, 128), (2, 129), (70000, 2), (1 << 22, 1), (8200, 129)])
 def test_csr_of_many_rows(gpu_lib, heads, nb):
-    """131200 rows (past the limit of the sums in the CSR kernel), row counts 4 does not divide,
-    4194304 heads (a 1024-thread group for each would be more than a grid holds)."""
+    """Row counts 4 does not divide, 4194304 heads (a 1024-thread group for each would be more than a
+    grid holds) and 1057800 rows of two groups a head (both past the limit of the sums in the CSR kernel)."""
     w = gpu_lib
     rng = np.random.default_rng(heads)
     s = w.make_shape(1, heads, 64 * nb, 64, 64)

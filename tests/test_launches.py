@@ -83,3 +83,9 @@ def test_csr_groups_hold_whole_heads(recorder, heads, nb):
     (x, y), = [(f[2], f[3]) for f in launches if f[1] == "csr_kernel"]
     per = min(max(1, 128 // nb), -(-heads // 512))
     assert (x, y) == (-(-heads // per), -(-nb // 128))
+
+
+@pytest.mark.parametrize("heads,nb,scan", [(1024, 128, False), (8192, 128, False), (8128, 129, False), (8200, 129, True), (1 << 22, 1, True)])
+def test_scan_only_past_the_sums(recorder, heads, nb, scan):
+    launches, status = recorder("masks", 1, heads, 64 * nb, 64, 64)
+    assert status == 0 and [f[1] for f in launches] == ["union_rows_kernel"] + ["scan_kernel"] * scan + ["csr_kernel"]
