@@ -75,3 +75,24 @@ def test_csr_of_many_rows(gpu_lib, heads, nb):
     assert np.array_equal(sched.row_ptr.cpu().numpy(), rp)
     assert np.array_equal(sched.col_idx[: rp[-1]].cpu().numpy(), np.nonzero(bits)[1])
     assert np.array_equal(sched.row_order.cpu().numpy(), O.schedule_order(rp, nb))
+
+
+@pytest.mark.parametrize("kind", ["plain", "wide", "ties", "denormal", "odd", "peaked"])
+@pytest.mark.parametrize("nb", [11, 12, 13, 14])
+def test_step_around_the_ranked_rows(gpu_lib, kind, nb):
+    """Rows of up to 12 candidates are ranked, longer ones cut by digits."""
+    w = gpu_lib
+    heads = 40
+    acc = masses(kind, heads * nb, nb, np.random.default_rng(nb)).reshape(1, heads, nb, nb)
+    s = w.make_shape(1, heads, 64 * nb, 64, 64)
+    mask = torch.zeros(heads * nb, 1, dtype=torch.int64, device="cuda")
+    for tau in (0.3, 0.95, 1.0):
+        tau = float(np.float32(tau))
+        w.wise_select_step(s, torch.from_numpy(acc).cuda(), tau, mask)
+        torch.cuda.synchronize()
+        with np.errstate(invalid="ignore"):
+            rp, ci = O.select_support(acc.astype(np.float64), tau, 0)
+        got = np.unpackbits(mask.cpu().numpy().view(np.uint8), axis=1, bitorder="little")[:, :nb]
+        want = np.zeros_like(got)
+        want[np.repeat(np.arange(heads * nb), np.diff(rp)), ci] = 1
+        assert np.array_equal(got, want), (kind, nb, tau)
