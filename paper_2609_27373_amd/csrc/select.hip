@@ -138,17 +138,19 @@ __device__ int cut_by_rank(const float x[E], int cnt, double tau, uint64_t* lds,
 // of 2^-53 times a power of two above their sum: so for the heavy masses
 // (exponent at most 28 below the total's) the ordered prefix sums are plain
 // sums, and the cut is found digit by digit of the mass bits from sums per digit.  The light
-// masses only follow the heavy ones in the order; where there are at most 64
-// they are ranked and added one by one to give the total.  Returns false
-// (nothing decided) for negative, infinite or NaN masses, more light ones, or
-// a cut among them: cut_by_rank then does the row.  On success sel[e] tells
+// masses only follow the heavy ones in the order; they matter for the total,
+// which the ordered sum rounds at each of up to 1024 of them: the true one is
+// within 2^-43 of a sum in any order, and a cut that is the same at both ends
+// of that range (here 2^-42) is the cut.  Returns false (nothing decided) for
+// negative, infinite or NaN masses, a cut among the light ones, or one that
+// the range leaves open: cut_by_rank then does the row.  On success sel[e] tells
 // whether candidate lane + 64 e is among the first k*.
 // Bound by instruction issue: about four passes of E LDS adds and one 64-lane
 // scan, where ranking takes nb / 2 comparisons per candidate and a serial sum.
-// Whole selection, both ways: 28160 rows of 128 blocks 108.3 -> 30.0 us (of
-// which this kernel about 24), 8192 rows of 128 41.6 -> 19.1 us, 8192 rows of
-// 1024 blocks 615 -> 88.6 us (cut_by_rank on every row, before the CSR's
-// change too).
+// wise_select_step, every row ranked / so: 28160 rows of 128 blocks 69.7 / 18.7
+// us on uniform masses, 69.6 / 12.8 on one heavy mass and light ones (70.4
+// where such rows were ranked to round their total); 8192 rows of 1024 blocks
+// 481 / 47 and 480 / 26.
 template <int E>
 __device__ bool cut_by_digits(const float x[E], int cnt, double tau, uint64_t* lds, int lane,
                               bool sel[E]) {
@@ -170,39 +172,18 @@ __device__ bool cut_by_digits(const float x[E], int cnt, double tau, uint64_t* l
   const int e0 = max(et + 127 - 28, 0);
   const uint32_t heavy = (uint32_t)e0 << 23;            // smallest heavy mass bits
   double hp = 0.0;
-  int light = 0;
+  bool light = false;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     if (u[e] >= heavy) hp += (double)__builtin_bit_cast(float, u[e]);
-    light += __builtin_popcountll(__builtin_amdgcn_ballot_w64(u[e] > 0 && u[e] < heavy));
+    else light = light || u[e] > 0;
   }
   const double big = wave_sum(hp);
-  double total = big;
-  if (light > 64) return false;
-  if (light > 0) {
-    uint32_t* lu = (uint32_t*)lds;
-    int at = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const bool l = u[e] > 0 && u[e] < heavy;
-      const uint64_t b = __builtin_amdgcn_ballot_w64(l);
-      if (l) lu[at + __builtin_popcountll(b & ((1ull << lane) - 1ull))] = u[e];
-      at += __builtin_popcountll(b);
-    }
-    wave_sync();
-    const uint32_t mine = lane < light ? lu[lane] : 0u;
-    int rank = 0;
-    for (int c = 0; c < light; ++c) {
-      const uint32_t o = lu[c];
-      rank += (o > mine || (o == mine && c < lane)) ? 1 : 0;
-    }
-    wave_sync();
-    if (lane < light) lu[rank] = mine;
-    wave_sync();
-    for (int r = 0; r < light; ++r) total += (double)__builtin_bit_cast(float, lu[r]);
-    wave_sync();
+  double low = tau * big, thr = low;                    // the threshold is in low .. thr
+  if (__builtin_amdgcn_ballot_w64(light)) {
+    low = tau * (about * (1.0 - 0x1p-42));
+    thr = tau * (about * (1.0 + 0x1p-42));
   }
-  const double thr = tau * total;
   if (thr > big) return false;
   double* bins = (double*)lds;
   uint32_t head = 0;                                    // leading bits of the cut's mass
@@ -258,7 +239,12 @@ __device__ bool cut_by_digits(const float x[E], int cnt, double tau, uint64_t* l
   // blocks first, as reach the threshold.
   const double val = (double)__builtin_bit_cast(float, cut);
   int need = 0;
-  for (double c = above; c < thr; c += val) ++need;
+  double shorter = above;                               // the sum without the last of them
+  for (double c = above; c < thr; c += val) {
+    shorter = c;
+    ++need;
+  }
+  if (shorter >= low) return false;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const uint64_t b = __builtin_amdgcn_ballot_w64(u[e] == cut);

@@ -1,6 +1,6 @@
 """Selection where its paths meet: sums by digit against ranked rows (masses
 whose fp64 sums round, negative and infinite ones, ties at the cut, light
-masses few and many), chunk edges of the CSR kernel, and row counts past the
+masses few and many and at the threshold's last bit), chunk edges of the CSR kernel, and row counts past the
 limit of its sums.  Bit for bit the oracle's."""
 
 import numpy as np
@@ -29,10 +29,19 @@ def masses(kind, rows, nb, rng):
         x[2::7, 0] = np.inf
     elif kind == "peaked":
         x = (x ** 40).astype(np.float32)
+    elif kind == "edge":        # tau 0.5: the threshold is the first mass, or one rounding above it, by the sum of 128 light ones
+        x[:] = 0
+        x[:, 0] = 0.5 + 2.0 ** -23
+        x[:, 1:2] = 0.5 - 2.0 ** -23
+        x[:, 2:130] = 2.0 ** -29
+        x[1::2, 60:61] *= np.float32(1 + 2.0 ** -23)
+        x[2::3, 90:91] *= np.float32(1 + 2.0 ** -21)
+    elif kind == "mixed":       # a few heavy ones, light ones of every size below
+        x = np.where(rng.random((rows, nb)) < 0.03, x, x * np.exp2(-rng.integers(27, 70, (rows, nb)))).astype(np.float32)
     return x
 
 
-@pytest.mark.parametrize("kind", ["plain", "wide", "light", "ties", "denormal", "odd", "peaked"])
+@pytest.mark.parametrize("kind", ["plain", "wide", "light", "ties", "denormal", "odd", "peaked", "edge", "mixed"])
 @pytest.mark.parametrize("nb", [1, 2, 64, 127, 129, 300, 1024])
 def test_selection_paths(gpu_lib, kind, nb):
     w = gpu_lib
