@@ -565,10 +565,10 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
   constexpr int kEPT = kKeyTile / kE;               // entries per 64-key tile
   constexpr int kParts = kMass ? (kE == 16 ? 4 : 2) : 0;
   constexpr int R = dense_ring(NW);
-  constexpr int kLds = R > 0 ? 2 * R * Swizzle<D>::kTile : 2 * (G::kKElems + G::kVElems);
-  __shared__ __attribute__((aligned(1024))) char smem[kLds];
-  uint16_t* const ks = (uint16_t*)smem;
-  uint16_t* const vt = ks + G::kKElems;
+  __shared__ __attribute__((aligned(1024))) char smem[R > 0 ? 2 * R * Swizzle<D>::kTile : 1];   // rings
+  // The staged tile: two arrays, so that the compiler need not order one's
+  // stores and the other's reads (1088 x 12 heads of 128: 26.0 us, 29.8 in one).
+  __shared__ __attribute__((aligned(16))) uint16_t ks[R > 0 ? 1 : G::kKElems], vt[R > 0 ? 1 : G::kVElems];
   int bh, item;
   if (!sched_slot(sc, bh, item)) return;
   const int qt = sc.items - 1 - item;
