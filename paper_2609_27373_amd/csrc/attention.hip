@@ -301,6 +301,26 @@ struct WaveRows {
     return pair_max(mx) * c;
   }
 
+  // S^T of a swizzled 64-key tile, and O^T += V^T P^T from one.
+  __device__ __forceinline__ void scores_swizzled(const char* kt, const ReadAddr<D>& ra, f32x16_t s[2]) const {
+#pragma unroll
+    for (int i = 0; i < G::kDChunks; ++i)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        s[t] = mfma32x32x16(*(const u32x4_t*)(kt + ra.k[i] + 32 * t * Swizzle<D>::kRow), qf[i], s[t]);
+  }
+  __device__ __forceinline__ void pv_swizzled(const char* vt, const ReadAddr<D>& ra, const u32x4_t pb[4]) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int t = 0; t < G::kDTiles; ++t) {
+        const char* p = vt + ra.v[t] + 16 * ks * Swizzle<D>::kRow;
+        const u32x2_t lo = lds_read_tr16((const uint16_t*)p);
+        const u32x2_t hi = lds_read_tr16((const uint16_t*)(p + 4 * Swizzle<D>::kRow));
+        o[t] = mfma32x32x16(u32x4_t{lo[0], lo[1], hi[0], hi[1]}, pb[ks], o[t]);
+      }
+  }
+
   // New running max from a tile's max mx; true (wave-uniform) when some
   // query's max grew: alpha then holds the factor of O, l is rescaled here.
   __device__ __forceinline__ bool raise_max(float mx, float& alpha) {
@@ -836,19 +856,27 @@ struct RowIds {
 // first, so an XCD works through a few heads at a time and their K/V tiles
 // stay in its L2.
 //
-// Bound by the round trip of a tile to L2 and beyond: what counts is groups
-// per CU and how long their copies have to land.  K and V are copied straight
-// into LDS, one tile each without row pads (32 KB at d 128), the next K after
-// S^T and the next V after PV, each with half a tile of work to land; with no
-// tile in registers d 128 takes 191 VGPRs instead of 255 and five groups fit
-// the LDS of a CU instead of four (three waves per SIMD at d 64 and 96; at d
-// 128 they would spill 42 VGPRs).  Four barriers per tile, of two or four waves,
-// cost less than that gives.  Against tiles staged through registers:
-// 64-key blocks 4096 x 32 heads of 128 at density 0.43 95.9 -> 88.0 us, 110
-// heads of 96 at 0.52 284 -> 252, 128 grouped heads of 64 at 0.56 220 -> 210;
-// 128-key blocks 4096 x 32 heads of 128 at 0.65 108.6 -> 102.0.  Same bits.
+// Bound by the round trip of a tile to L2 and beyond: what counts is how many
+// copies are in flight on a CU and how long they have to land.  K and V are
+// copied straight into LDS without row pads, no tile waits in registers (133,
+// 160 and 191 VGPRs at d 64, 96 and 128: 3, 3 and 2 waves per SIMD).
+//   kBufs 1   one tile each, 32 KB at d 128: the next K is copied after S^T,
+//             the next V after PV, each with half a tile of work to land, and
+//             four barriers a tile.  Registers, not LDS, limit the groups of a
+//             CU (six 2-wave groups, four at d 128).
+//   kBufs 2   two tiles each: both copies have a whole tile to land and one
+//             barrier is enough.  4-wave groups (128-key blocks) still fit
+//             four, three and two to a CU; of 2-wave groups LDS then holds
+//             five, three and two, so they take it in small grids only
+//             (kSmallGrid).
+// us, tiles staged through registers / one tile / two: 64-key blocks at density
+// 0.3 (about 0.3 of the causal blocks, drawn at random), 2048 x 4 heads of 64
+// 15.8 / 16.8 / 14.5, 4096 x 16 heads of 96 43.0 / 41.6 / 38.8, 4096 x 55 of 96
+// 106 / 95 / 108, 4096 x 32 of 128 73.9 / 71.0 / 88; 128-key blocks, 2048 x 16
+// grouped heads of 64 (density 1) 33.3 / 36.9 / 28.9, 4096 x 32 of 128 (0.7)
+// 130 / 124 / 118, 4096 x 55 of 96 (0.3) 103 / 98.5 / 95.1.  Same bits.
 // ---------------------------------------------------------------------------
-template <int D, int NW>
+template <int D, int NW, int kBufs>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3)))
 sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
                    const uint16_t* __restrict__ V, const int32_t* __restrict__ row_ptr,
@@ -861,7 +889,9 @@ sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
   constexpr int kP = D / 32;                        // 1 KB copies per 16 rows
   constexpr int kU = 4 / NW, kC = kU * kP;          // a wave's 16-row pieces and copies of a tile
   static_assert(kTPB >= 1 && kB % kKeyTile == 0 && 4 % NW == 0, "block / key tile");
-  __shared__ __attribute__((aligned(1024))) char kt[kTile], vt[kTile];
+  extern __shared__ __attribute__((aligned(1024))) char tiles[];   // kBufs K tiles, kBufs V tiles
+  const char* const kt = tiles;
+  const char* const vt = tiles + kBufs * kTile;
   int sh, sit;
   if (!sched_slot(sc, sh, sit)) return;
   const int row = order ? order[sh * nb + sit] : sh * nb + (nb - 1 - sit);
@@ -914,45 +944,54 @@ sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
     copy(bk, ko, key0, lk);
     copy(bv, vo, key0, lv);
   }
-  while (key0 >= 0) {
-    const int next = next_key();
-    const bool mine = key0 <= q0;                   // else the tile lies past this wave's queries
-    wait_copies<kC>();                              // this tile's K; its V may be in flight
-    __syncthreads();
-    f32x16_t s[2] = {f32x16_t{}, f32x16_t{}};
-    if (mine) {
-#pragma unroll
-      for (int i = 0; i < G::kDChunks; ++i)
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-          s[t] = mfma32x32x16(*(const u32x4_t*)(kt + ra.k[i] + 32 * t * kRow), w.qf[i], s[t]);
+  if constexpr (kBufs == 2) {
+    auto step = [&](auto buf) {                     // the tile in buffer buf; true: there is another
+      constexpr int kOther = 1 - decltype(buf)::value;
+      const int next = next_key();
+      wait_copies<0>();
+      __syncthreads();                              // it has landed and the one before is read, for every wave
+      if (next >= 0) {
+        copy(bk, ko, next, lk + kOther * kTile);
+        copy(bv, vo, next, lv + kOther * kTile);
+      }
+      if (key0 <= q0) {                             // else the tile lies past this wave's queries
+        f32x16_t s[2] = {f32x16_t{}, f32x16_t{}};
+        u32x4_t pb[4];
+        w.scores_swizzled(kt + decltype(buf)::value * kTile, ra, s);
+        if (key0 + kKeyTile - 1 > q0) WaveRows<D>::template mask<2>(s, key0, q0 + (lane & 31), lane);
+        w.template softmax<2>(s, pb, c);
+        w.pv_swizzled(vt + decltype(buf)::value * kTile, ra, pb);
+      }
+      key0 = next;
+      return next >= 0;
+    };
+    if (key0 >= 0)
+      while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{})) {}
+  } else {
+    while (key0 >= 0) {
+      const int next = next_key();
+      const bool mine = key0 <= q0;                 // else the tile lies past this wave's queries
+      wait_copies<kC>();                            // this tile's K; its V may be in flight
+      __syncthreads();
+      f32x16_t s[2] = {f32x16_t{}, f32x16_t{}};
+      if (mine) w.scores_swizzled(kt, ra, s);
+      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();                              // K read: its place is free
+      if (next >= 0) copy(bk, ko, next, lk);
+      u32x4_t pb[4];
+      if (mine) {
+        if (key0 + kKeyTile - 1 > q0) WaveRows<D>::template mask<2>(s, key0, q0 + (lane & 31), lane);
+        w.template softmax<2>(s, pb, c);
+      }
+      if (next >= 0) wait_copies<kC>();             // this tile's V; the next K may be in flight
+      else wait_copies<0>();
+      __syncthreads();
+      if (mine) w.pv_swizzled(vt, ra, pb);
+      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();                              // V read: its place is free
+      if (next >= 0) copy(bv, vo, next, lv);
+      key0 = next;
     }
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();                                // K read: its place is free
-    if (next >= 0) copy(bk, ko, next, lk);
-    u32x4_t pb[4];
-    if (mine) {
-      if (key0 + kKeyTile - 1 > q0) WaveRows<D>::template mask<2>(s, key0, q0 + (lane & 31), lane);
-      w.template softmax<2>(s, pb, c);
-    }
-    if (next >= 0) wait_copies<kC>();               // this tile's V; the next K may be in flight
-    else wait_copies<0>();
-    __syncthreads();
-    if (mine) {
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-        for (int t = 0; t < G::kDTiles; ++t) {
-          const char* p = vt + ra.v[t] + 16 * ks * kRow;
-          const u32x2_t lo = lds_read_tr16((const uint16_t*)p);
-          const u32x2_t hi = lds_read_tr16((const uint16_t*)(p + 4 * kRow));
-          w.o[t] = mfma32x32x16(u32x4_t{lo[0], lo[1], hi[0], hi[1]}, pb[ks], w.o[t]);
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();                                // V read: its place is free
-    if (next >= 0) copy(bv, vo, next, lv);
-    key0 = next;
   }
   w.finish(O + hoff, lse ? lse + (size_t)bh * n : nullptr, q0, lane);
 }
@@ -1481,6 +1520,32 @@ size_t mass_workspace_bytes(const Dims& s) {
   return (size_t)s.bh * qt * (qt / e) * (nq * (nq + 1) / 2) * sizeof(float);
 }
 
+// 64-key-block rows up to which a group holds two tiles of each (sparse_attn_kernel).
+// us with one / two, 4096 tokens, every block kept: d 64, 16 heads (1024 rows)
+// 67.4 / 64.5, 17 heads at density 0.3 35.7 / 38.7; d 96, 20 heads 96.1 / 93.6,
+// 24 heads 107 / 111; d 128, 12 heads 93.9 / 90.0, 14 heads 97.4 / 109.
+template <int D>
+constexpr int kSmallGrid = D == 64 ? 1024 : D == 96 ? 1280 : 768;
+
+// LDS that a group leaves unused, so that four and not six groups of 64-key
+// rows of d 96 share a CU.  With fewer than 2048 rows (8 groups a CU) six at once leave
+// too few to even out what the first ones differ by; where the heads are not
+// shared out over the XCDs (Sched::per_xcd 0), six walk more keys at a time than the
+// L2s hold.  us with six / four, 4096 tokens at density 0.3 and 1: 22 heads 60.8 /
+// 54.5 and 136 / 125, 30 heads 64.5 / 58.3 and 148 / 142, 33 heads at 1 210 / 192;
+// 32 heads at 0.3 55.0 / 58.4.
+template <int D>
+static unsigned idle_lds(const Sched& sc, int rows) {
+  return D == 96 && (rows < 2048 || sc.per_xcd == 0) ? 40960 - 2 * Swizzle<D>::kTile : 0;
+}
+
+template <int D, int NW, int kBufs>
+static void launch_rows_of(const Dims& s, const Sched& sc, unsigned idle, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
+                           const int32_t* rp, const int32_t* ci, const int32_t* order, uint16_t* o, float* lse, hipStream_t st) {
+  hipLaunchKernelGGL((sparse_attn_kernel<D, NW, kBufs>), dim3(sched_grid(sc)), dim3(NW * 64), 2 * kBufs * Swizzle<D>::kTile + idle, st,
+                     Q, K, V, rp, ci, order, o, lse, s.n, s.nb, s.bh * s.nb, s.heads, s.gq, sc, s.scale * kLog2e);
+}
+
 template <int D>
 static hipError_t launch_sparse_d(const Dims& s, const void* q, const void* k, const void* v,
                                   const int32_t* rp, const int32_t* ci, const int32_t* order,
@@ -1498,12 +1563,12 @@ static hipError_t launch_sparse_d(const Dims& s, const void* q, const void* k, c
   else if (s.block == 32)
     hipLaunchKernelGGL((sparse_row32_kernel<D>), grid, dim3(64), 0, st, Q, K, V, rp, ci, order,
                        (uint16_t*)o, lse, s.n, s.nb, rows, s.heads, s.gq, sc, c);
-  else if (s.block == 64)
-    hipLaunchKernelGGL((sparse_attn_kernel<D, 2>), grid, dim3(128), 0, st, Q, K, V, rp, ci,
-                       order, (uint16_t*)o, lse, s.n, s.nb, rows, s.heads, s.gq, sc, c);
+  else if (s.block == 128)
+    launch_rows_of<D, 4, 2>(s, sc, 0, Q, K, V, rp, ci, order, (uint16_t*)o, lse, st);
+  else if (rows <= kSmallGrid<D>)
+    launch_rows_of<D, 2, 2>(s, sc, 0, Q, K, V, rp, ci, order, (uint16_t*)o, lse, st);
   else
-    hipLaunchKernelGGL((sparse_attn_kernel<D, 4>), grid, dim3(256), 0, st, Q, K, V, rp, ci,
-                       order, (uint16_t*)o, lse, s.n, s.nb, rows, s.heads, s.gq, sc, c);
+    launch_rows_of<D, 2, 1>(s, sc, idle_lds<D>(sc, rows), Q, K, V, rp, ci, order, (uint16_t*)o, lse, st);
   return hipGetLastError();
 }
 

@@ -47,7 +47,7 @@ hip_error hipLaunchKernel(const void* f, dim3_t g, dim3_t b, void** args, size_t
     if (table[i].stub == f) name = table[i].name;
   const int ok = g.x > 0 && g.y > 0 && g.z > 0 && (uint64_t)g.x * b.x < (1ull << 32) && (uint64_t)g.y * b.y < (1ull << 32) &&
                  g.y < 65536 && g.z < 65536 && (uint64_t)b.x * b.y * b.z <= 1024 && lds <= 65536;
-  printf("%s %s %u %u %u %u\n", ok ? "launch" : "refused", name, g.x, g.y, g.z, b.x);
+  printf("%s %s %u %u %u %u %zu\n", ok ? "launch" : "refused", name, g.x, g.y, g.z, b.x, lds);
   if (!ok) last = 9;
   return ok ? 0 : 9;
 }

@@ -28,14 +28,15 @@ def recorder(tmp_path_factory):
                     f"-Wl,-rpath,{os.path.dirname(wise.LIB_PATH)}"], check=True, capture_output=True, text=True)
 
     def record(entry, batch, heads, n, d, block, option=1, kv_heads=1):
-        """([(verdict, kernel, grid x, y, z, threads)], status) of one call."""
+        """([(verdict, kernel, grid x, y, z, threads, dynamic LDS, template arguments)], status) of one call."""
         line = f"{entry} {batch} {heads} {kv_heads} {n} {d} {block} {option}\n"
         out = subprocess.run([str(exe)], input=line, capture_output=True, text=True, timeout=60, check=True).stdout.split("\n")
         launches = []
         for ln in out:
             f = ln.split()
             if f and f[0] in ("launch", "refused"):
-                launches.append((f[0], re.search(r"\d+([a-z]+(?:_[a-z0-9]+)*_kernel)", f[1]).group(1), *map(int, f[2:])))
+                launches.append((f[0], re.search(r"\d+([a-z]+(?:_[a-z0-9]+)*_kernel)", f[1]).group(1), *map(int, f[2:]),
+                                 tuple(int(x) for x in re.findall(r"Li(\d+)E", f[1]))))
         return launches, int(out[-2].split()[1])
 
     return record
@@ -46,7 +47,7 @@ WISE_ERR_HIP = 6
 
 def test_recorder(recorder):
     launches, status = recorder("dense", 1, 32, 4096, 128, 64, kv_heads=32)
-    assert status == 0 and launches == [("launch", "dense_attn_kernel", 512, 1, 1, 512)]
+    assert status == 0 and launches == [("launch", "dense_attn_kernel", 512, 1, 1, 512, 0, (128, 8, 0))]
 
 
 # 2^26 rows: 64 threads each are more than a grid holds
@@ -89,3 +90,15 @@ def test_csr_groups_hold_whole_heads(recorder, heads, nb):
 def test_scan_only_past_the_sums(recorder, heads, nb, scan):
     launches, status = recorder("masks", 1, heads, 64 * nb, 64, 64)
     assert status == 0 and [f[1] for f in launches] == ["union_rows_kernel"] + ["scan_kernel"] * scan + ["csr_kernel"]
+
+
+# One row a work-group of 64- and 128-key blocks: two tiles in LDS for 128-key blocks and in small grids, and
+# at d 96 four groups a CU where the grid is not large or its heads are not shared out over the XCDs
+@pytest.mark.parametrize("d,block,heads,nb,bufs,lds", [
+    (64, 64, 16, 64, 2, 32768), (64, 64, 17, 64, 1, 16384), (96, 64, 20, 64, 2, 49152), (96, 64, 21, 64, 1, 40960), (96, 64, 31, 64, 1, 40960),
+    (96, 64, 32, 64, 1, 24576), (96, 64, 33, 64, 1, 40960), (128, 64, 12, 64, 2, 65536), (128, 64, 13, 64, 1, 32768),
+    (64, 128, 2, 4, 2, 32768), (96, 128, 200, 32, 2, 49152), (128, 128, 64, 128, 2, 65536)])
+def test_late_rows_route(recorder, d, block, heads, nb, bufs, lds):
+    (launch,), status = recorder("sparse", 1, heads, nb * block, d, block)
+    assert status == 0 and launch[0] == "launch" and launch[1] == "sparse_attn_kernel"
+    assert launch[5:] == (block * 2, lds, (d, block // 32, bufs))
