@@ -26,8 +26,8 @@
 // a row is exactly 1 in bf16); the O rescale is skipped, wave-uniformly, on
 // tiles that raise no row's max.
 //
-// Work order: see sched_slot (heaviest items of every head first, heads
-// grouped per XCD).
+// Work order: see sched_slot and row_slot (heaviest items of every head first,
+// heads grouped per XCD).
 #include <algorithm>
 #include <type_traits>
 
@@ -882,7 +882,7 @@ sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
                    const uint16_t* __restrict__ V, const int32_t* __restrict__ row_ptr,
                    const int32_t* __restrict__ col_idx, const int32_t* __restrict__ order,
                    uint16_t* __restrict__ O, float* __restrict__ lse, int n, int nb, int rows,
-                   int heads, int gq, Sched sc, float c) {
+                   int heads, int gq, RowSched sc, float c) {
   using G = Geo<D>;
   constexpr int kB = NW * 32, kTPB = kB / kKeyTile;
   constexpr int kRow = Swizzle<D>::kRow, kTile = Swizzle<D>::kTile;   // bytes
@@ -893,7 +893,7 @@ sparse_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ 
   const char* const kt = tiles;
   const char* const vt = tiles + kBufs * kTile;
   int sh, sit;
-  if (!sched_slot(sc, sh, sit)) return;
+  if (!row_slot(sc, sh, sit)) return;
   const int row = order ? order[sh * nb + sit] : sh * nb + (nb - 1 - sit);
   if ((unsigned)row >= (unsigned)rows) return;
   const int bh = row / nb, qb = row % nb;
@@ -1185,13 +1185,13 @@ sparse_row32_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
                     const uint16_t* __restrict__ V, const int32_t* __restrict__ row_ptr,
                     const int32_t* __restrict__ col_idx, const int32_t* __restrict__ order,
                     uint16_t* __restrict__ O, float* __restrict__ lse, int n, int nb, int rows,
-                    int heads, int gq, Sched sc, float c) {
+                    int heads, int gq, RowSched sc, float c) {
   using G = Geo<D>;
   constexpr int kC = D / 32;                        // 1 KB copies per 16 rows
   constexpr int kRow = 2 * D, kTile = 32 * kRow;    // bytes
   __shared__ __attribute__((aligned(1024))) char kt[kTile], vt[kTile];
   int sh, sit;
-  if (!sched_slot(sc, sh, sit)) return;
+  if (!row_slot(sc, sh, sit)) return;
   const int row = order ? order[sh * nb + sit] : sh * nb + (nb - 1 - sit);
   if ((unsigned)row >= (unsigned)rows) return;
   const int bh = row / nb, qb = row % nb;
@@ -1288,13 +1288,13 @@ sparse_row16_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
                     const uint16_t* __restrict__ V, const int32_t* __restrict__ row_ptr,
                     const int32_t* __restrict__ col_idx, const int32_t* __restrict__ order,
                     uint16_t* __restrict__ O, float* __restrict__ lse, int n, int nb, int rows,
-                    int heads, int gq, Sched sc, float c) {
+                    int heads, int gq, RowSched sc, float c) {
   constexpr int kC = D / 32;                        // MFMAs of a block's S^T; 1 KB copies of its V
   constexpr int kT = D / 16;                        // MFMAs of PV
   constexpr int kRow = 2 * D, kBlock = 16 * kRow;   // bytes
   __shared__ __attribute__((aligned(1024))) char kt[2 * kBlock], vt[2 * kBlock];
   int sh, sit;
-  if (!sched_slot(sc, sh, sit)) return;
+  if (!row_slot(sc, sh, sit)) return;
   const int row = order ? order[sh * nb + sit] : sh * nb + (nb - 1 - sit);
   if ((unsigned)row >= (unsigned)rows) return;
   const int bh = row / nb, qb = row % nb;
@@ -1528,21 +1528,19 @@ template <int D>
 constexpr int kSmallGrid = D == 64 ? 1024 : D == 96 ? 1280 : 768;
 
 // LDS that a group leaves unused, so that four and not six groups of 64-key
-// rows of d 96 share a CU.  With fewer than 2048 rows (8 groups a CU) six at once leave
-// too few to even out what the first ones differ by; where the heads are not
-// shared out over the XCDs (Sched::per_xcd 0), six walk more keys at a time than the
-// L2s hold.  us with six / four, 4096 tokens at density 0.3 and 1: 22 heads 60.8 /
-// 54.5 and 136 / 125, 30 heads 64.5 / 58.3 and 148 / 142, 33 heads at 1 210 / 192;
-// 32 heads at 0.3 55.0 / 58.4.
+// rows of d 96 share a CU.  With fewer than 2048 rows (8 groups a CU) six at once
+// leave too few to even out what the first ones differ by.  us with six / four,
+// 4096 tokens at density 0.3 and 1: 22 heads 60.8 / 54.5 and 136 / 125, 30 heads
+// 64.5 / 58.3 and 148 / 142; 32 heads at 0.3 55.0 / 58.4.
 template <int D>
-static unsigned idle_lds(const Sched& sc, int rows) {
-  return D == 96 && (rows < 2048 || sc.per_xcd == 0) ? 40960 - 2 * Swizzle<D>::kTile : 0;
+static unsigned idle_lds(int rows) {
+  return D == 96 && rows < 2048 ? 40960 - 2 * Swizzle<D>::kTile : 0;
 }
 
 template <int D, int NW, int kBufs>
-static void launch_rows_of(const Dims& s, const Sched& sc, unsigned idle, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
+static void launch_rows_of(const Dims& s, const RowSched& sc, unsigned idle, const uint16_t* Q, const uint16_t* K, const uint16_t* V,
                            const int32_t* rp, const int32_t* ci, const int32_t* order, uint16_t* o, float* lse, hipStream_t st) {
-  hipLaunchKernelGGL((sparse_attn_kernel<D, NW, kBufs>), dim3(sched_grid(sc)), dim3(NW * 64), 2 * kBufs * Swizzle<D>::kTile + idle, st,
+  hipLaunchKernelGGL((sparse_attn_kernel<D, NW, kBufs>), dim3(row_grid(sc)), dim3(NW * 64), 2 * kBufs * Swizzle<D>::kTile + idle, st,
                      Q, K, V, rp, ci, order, o, lse, s.n, s.nb, s.bh * s.nb, s.heads, s.gq, sc, s.scale * kLog2e);
 }
 
@@ -1555,8 +1553,8 @@ static hipError_t launch_sparse_d(const Dims& s, const void* q, const void* k, c
   const auto* K = (const uint16_t*)k;
   const auto* V = (const uint16_t*)v;
   const int rows = s.bh * s.nb;
-  const Sched sc = make_sched(s.bh, s.nb, (size_t)s.n * D * 4 / s.gq);
-  const dim3 grid(sched_grid(sc));
+  const RowSched sc = make_row_sched(s.bh, s.nb, (size_t)s.n * D * 4 / s.gq, s.block < 64);
+  const dim3 grid(row_grid(sc));
   if (s.block == 16)
     hipLaunchKernelGGL((sparse_row16_kernel<D>), grid, dim3(64), 0, st, Q, K, V, rp, ci, order,
                        (uint16_t*)o, lse, s.n, s.nb, rows, s.heads, s.gq, sc, c);
@@ -1568,7 +1566,7 @@ static hipError_t launch_sparse_d(const Dims& s, const void* q, const void* k, c
   else if (rows <= kSmallGrid<D>)
     launch_rows_of<D, 2, 2>(s, sc, 0, Q, K, V, rp, ci, order, (uint16_t*)o, lse, st);
   else
-    launch_rows_of<D, 2, 1>(s, sc, idle_lds<D>(sc, rows), Q, K, V, rp, ci, order, (uint16_t*)o, lse, st);
+    launch_rows_of<D, 2, 1>(s, sc, idle_lds<D>(rows), Q, K, V, rp, ci, order, (uint16_t*)o, lse, st);
   return hipGetLastError();
 }
 

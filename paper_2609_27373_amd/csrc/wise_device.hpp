@@ -261,4 +261,64 @@ __device__ __forceinline__ bool sched_slot(const Sched& s, int& head, int& item)
   return item < s.items;   // a short last group leaves empty slots
 }
 
+// Work order of the one-row late kernels: a Sched, or (split != 0) every head
+// as 8 parts, part p its items 8 i + p, and XCD x with the parts x * heads ..
+// (x + 1) * heads - 1 of all heads' parts: an even share and at most ceil(heads
+// / 8) + 1 heads whatever the head count.  An XCD walks its parts in groups of 8
+// * group, item-major inside a group.
+struct RowSched : Sched {
+  int split;
+};
+
+// Under a Sched two grids find little in L2, the less the more rows a CU holds:
+// heads that 8 XCDs don't share evenly run item-major over all XCDs, so every L2
+// sees every head's keys, and heads that 8 divides run all at once, however
+// many an XCD has.  The first are split, the second taken a few at a time where
+// rows are one wave (8 to 20 a CU).  us at density 0.3, as Sched / so: 16-key
+// blocks, 4096 x 33 heads of 96 251 / 85, x 88 of 128 679 / 308; 32-key, 4096 x
+// 33 of 96 132 / 63, 6912 x 88 grouped heads of 128 911 / 530; 64-key, 4096 x
+// 33 of 128 109 / 71.  (6912 x 88 at 0.65: 93 million L2 misses as Sched, 43
+// with the fewer waves that staging through registers left on a CU.)
+// One group while the XCD's keys and values are at most 8 MiB (32-key blocks,
+// 4096 x 33 of 96: 62 us, 78 two heads at a time; 2048 x 64 of 128 as Sched 48.7,
+// 57 three at a time), else as many heads as about 3 MiB holds, but the 384
+// rows that fill an XCD (128-key blocks, 4096 x 36 of 128: 174, 208 one at a time).
+inline RowSched make_row_sched(int heads, int items, size_t kv_bytes, bool one_wave) {
+  RowSched s{make_sched(heads, items, kv_bytes), 0};
+  const bool crowded = kv_bytes * heads / 8 > (size_t)(8u << 20);
+  const bool long_heads = kv_bytes >= (size_t)(4u << 20);
+  const size_t fit = (size_t)(long_heads && !one_wave ? 16u << 20 : 3u << 20) / (kv_bytes > 0 ? kv_bytes : 1);
+  const size_t fill = (size_t)(384 + items - 1) / items, few = fit > fill ? fit : fill;
+  if (s.per_xcd == 0) {
+    s.split = 1;
+    s.group = crowded && few < (size_t)heads ? (int)few : heads;
+  } else if (one_wave && crowded && (heads % 8 == 0 || long_heads)) {
+    s.group = few < (size_t)s.per_xcd ? (int)few : s.per_xcd;
+  }
+  return s;
+}
+
+inline unsigned row_grid(const RowSched& s) {
+  if (!s.split) return sched_grid(s);
+  const int per = s.group < s.heads / 8 ? 8 * s.group : s.heads;
+  const int64_t groups = (s.heads + per - 1) / per;
+  return (unsigned)(8 * groups * per * ((s.items + 7) / 8));
+}
+
+__host__ __device__ __forceinline__ bool split_slot(const RowSched& s, int block, int& head, int& item) {
+  const int chunks = (s.items + 7) >> 3, per = s.group < s.heads / 8 ? 8 * s.group : s.heads;
+  const int x = block & 7, j = block >> 3;
+  const int g = j / (per * chunks), r = j - g * per * chunks;
+  const int left = s.heads - g * per, parts = left < per ? left : per;
+  const int chunk = r / parts;
+  if (chunk >= chunks) return false;              // a short last group leaves empty slots
+  const int part = x * s.heads + g * per + r - chunk * parts;
+  head = part >> 3;
+  item = 8 * chunk + (part & 7);
+  return item < s.items;
+}
+__device__ __forceinline__ bool row_slot(const RowSched& s, int& head, int& item) {
+  return s.split ? split_slot(s, blockIdx.x, head, item) : sched_slot(s, head, item);
+}
+
 }  // namespace wise

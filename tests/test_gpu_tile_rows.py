@@ -49,8 +49,8 @@ def test_tile_rows_id_batches(gpu_lib, B, nb, d, kv_heads):
     assert_lse(lse, l_ref)
 
 
-# Rows (heads x blocks) up to the limit of the kernel with two tiles, one head more, the grid in which d 96 runs
-# four groups per CU (fewer than 2048 rows, or heads that 8 XCDs don't share evenly) and the one past it
+# Rows (heads x blocks) up to the limit of the kernel with two tiles, one head more (d 96: four groups per CU below
+# 2048 rows), and head counts that the XCDs share evenly (40, 32) or not
 @pytest.mark.parametrize("d,nb,heads", [(64, 64, (16, 17, 40)), (96, 64, (20, 21, 32, 33)), (128, 64, (12, 13, 40)), (64, 7, (146, 147)), (96, 1, (1280, 1281)),
                                         (128, 2, (384, 385))])
 def test_small_and_large_grids_give_the_same_bits(gpu_lib, d, nb, heads):
@@ -65,3 +65,37 @@ def test_small_and_large_grids_give_the_same_bits(gpu_lib, d, nb, heads):
     for other in out[1:]:
         assert all(torch.equal(a, b) for a, b in zip(out[0], other))
     assert torch.isfinite(out[0][0].float()).all()
+
+
+# Heads split over the XCDs (7, 17, 33) or taken a few at a time (88), and as they are (8): every block size, the same bits
+# for the heads that all grids have
+@pytest.mark.parametrize("B,d", [(16, 64), (16, 128), (32, 96), (32, 128), (64, 128), (128, 64)])
+def test_work_order_gives_the_same_bits(gpu_lib, B, d):
+    nb = 19
+    n = 64 * nb if B < 64 else B * nb
+    nb = n // B
+    g = torch.Generator(device="cuda").manual_seed(B + d)
+    q, k, v = (torch.randn((1, 88, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    rp, ci, _, _ = supports(88, nb, [0, 1, 2, 5, 17], np.random.default_rng(B))
+    out = []
+    for h in (8, 7, 17, 33, 88):
+        r = rp[: h * nb + 1]
+        o, lse = run(gpu_lib, *(x[:, :h].contiguous() for x in (q, k, v)), B, r, ci[: r[-1]])
+        out.append((o[:, :7], lse[:, :7]))
+    for other in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], other))
+
+
+def test_few_heads_at_a_time(gpu_lib):
+    """88 heads of 4096 tokens, 32-key blocks: an XCD's keys and values pass 8 MiB, so it takes its 11 heads three at a time;
+    a row's output does not depend on it."""
+    w, n, B, d = gpu_lib, 4096, 32, 64
+    nb = n // B
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn((1, 88, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    rp, ci, _, _ = supports(88, nb, [1, 2, 9], np.random.default_rng(7))
+    whole = run(w, q, k, v, B, rp, ci)
+    for h in (0, 30, 87):
+        lo, hi = rp[h * nb], rp[(h + 1) * nb]
+        one = run(w, *(x[:, h:h + 1].contiguous() for x in (q, k, v)), B, rp[h * nb:(h + 1) * nb + 1] - lo, ci[lo:hi])
+        assert torch.equal(one[0][:, 0], whole[0][:, h]) and torch.equal(one[1][:, 0], whole[1][:, h])

@@ -93,10 +93,10 @@ def test_scan_only_past_the_sums(recorder, heads, nb, scan):
 
 
 # One row a work-group of 64- and 128-key blocks: two tiles in LDS for 128-key blocks and in small grids, and
-# at d 96 four groups a CU where the grid is not large or its heads are not shared out over the XCDs
+# at d 96 four groups a CU in grids below 2048 rows
 @pytest.mark.parametrize("d,block,heads,nb,bufs,lds", [
     (64, 64, 16, 64, 2, 32768), (64, 64, 17, 64, 1, 16384), (96, 64, 20, 64, 2, 49152), (96, 64, 21, 64, 1, 40960), (96, 64, 31, 64, 1, 40960),
-    (96, 64, 32, 64, 1, 24576), (96, 64, 33, 64, 1, 40960), (128, 64, 12, 64, 2, 65536), (128, 64, 13, 64, 1, 32768),
+    (96, 64, 32, 64, 1, 24576), (96, 64, 33, 64, 1, 24576), (128, 64, 12, 64, 2, 65536), (128, 64, 13, 64, 1, 32768),
     (64, 128, 2, 4, 2, 32768), (96, 128, 200, 32, 2, 49152), (128, 128, 64, 128, 2, 65536)])
 def test_late_rows_route(recorder, d, block, heads, nb, bufs, lds):
     (launch,), status = recorder("sparse", 1, heads, nb * block, d, block)
