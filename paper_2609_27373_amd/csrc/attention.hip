@@ -20,8 +20,9 @@
 // probabilities are already in the B-operand layout of O^T = V^T P^T: they are
 // packed to bf16 in place and fed straight to the second MFMA chain.  V stays
 // row-major in LDS and its A-operand fragments are read transposed with
-// ds_read_b64_tr_b16; the 32-byte row pad makes those reads, like the 128-bit
-// K reads, free of bank conflicts.  Softmax is
+// ds_read_b64_tr_b16; row pads (2-wave dense and grouped kernels, which stage
+// tiles through registers) or permuted rows (Swizzle, the others) make those
+// reads, like the 128-bit K reads, free of bank conflicts.  Softmax is
 // online in base 2 with the exact running max (so the largest probability of
 // a row is exactly 1 in bf16); the O rescale is skipped, wave-uniformly, on
 // tiles that raise no row's max.
@@ -290,17 +291,6 @@ struct WaveRows {
     softmax_pv<H, kParts>(s, vt, lane, c);
   }
 
-  // Max over this lane's scores of one tile, times c, of the query (both halves).
-  template <int H>
-  __device__ __forceinline__ static float tile_max(const f32x16_t s[H], float c) {
-    float mx = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < H; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
-    return pair_max(mx) * c;
-  }
-
   // S^T of a swizzled 64-key tile, and O^T += V^T P^T from one.
   __device__ __forceinline__ void scores_swizzled(const char* kt, const ReadAddr<D>& ra, f32x16_t s[2]) const {
 #pragma unroll
@@ -345,9 +335,7 @@ struct WaveRows {
   // step leave nothing else to fill a wave's waits; mid(n, j) runs in slot j
   // (the copies).  The wave's priority falls through the step, so of the two
   // waves of a SIMD the one behind issues first and they reach the barrier
-  // together (3443 to 3186 cycles per tile at 16K).  Both the VALU (2790
-  // cycles without the MFMAs) and the matrix cores (2280 without the VALU
-  // work; 2048 at least) are then close to full.
+  // together.  VALU and matrix cores are then both close to full.
   template <int H, bool kQk, bool kPv, int kParts, class Mid, class Mask>
   __device__ __forceinline__ void step(const char* kn, const char* vt, const ReadAddr<D>& ra, int lane, float c,
                                        f32x16_t s[H], f32x16_t sn[H], float& mx, Mid mid, Mask maskn) {
@@ -562,14 +550,14 @@ constexpr int kMassBatch = 16;    // entry loads in flight per half-wave in the 
 
 // Tiles in each LDS ring of the dense group (0: one tile, staged through
 // registers).  An 8-wave group fills its CU alone, so its copies get two steps
-// to land; two 4-wave groups (and at d 64 five) share a CU and cover each
+// to land; two 4-wave groups (three at d 64) share a CU and cover each
 // other's waits, and four tiles each would leave one (d 96: 1242 us instead of
 // 796 at 8192 x 55 heads).  Rings against the staged loop, 4-wave groups: d 96,
-// 8192 x 55 heads 822 -> 796 us, with masses 890 -> 841, 1088 x 8 heads 21.7 ->
-// 19.8; d 64, 4096 x 192 grouped heads 506 -> 491, with 32-key masses 596 ->
-// 570; d 128, 640 x 4 heads 17.8 -> 15.5.  2-wave groups (lengths 128 does not
-// divide) stay staged: eight copies per wave and tile cost its two waves more
-// than the staging (1216 x 15 heads of 64: 24.0 against 22.0 us).
+// 4096 x 220 heads 825 -> 790 us, with 32-key masses 943 -> 886, 1024 x 32
+// grouped heads 24.0 -> 21.4; d 64, 4096 x 192 grouped heads 493 -> 467, with
+// 32-key masses 590 -> 574; d 128, 640 x 4 heads 18.1 -> 15.7.  2-wave groups
+// (lengths 128 does not divide) stay staged: eight copies per wave and tile cost
+// its two waves more than the staging (1216 x 15 heads of 64: 24.0 against 22.0).
 constexpr int dense_ring(int nw) { return nw == 8 ? 4 : nw == 4 ? 2 : 0; }
 
 template <int D, int NW, int BM>
@@ -634,12 +622,9 @@ dense_attn_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K
     // rings of R K and R V tiles.  At d 128, R = 4 (128 KB of LDS; registers
     // already limit a CU to one 8-wave group), copies have two steps to land:
     // one step is less than the latency of a tile from HBM (16K: 1.01x instead
-    // of 1.06x of the unpipelined loop).  Measured against that loop (S^T,
-    // softmax and PV one after the other, tiles staged through registers):
-    // 4096 x 32 heads 142 -> 134 us, 16384 x 64 heads 4069 -> 3827 us (1081
-    // -> 1149 TFLOP/s, 3105 cycles per tile instead of about 3900 at a clock
-    // that power holds at 1.7 instead of 1.95 GHz), 2048 x 16 heads 58.7 ->
-    // 51.9 us.
+    // of 1.06x of the unpipelined loop).  Against that loop (S^T, softmax and PV
+    // one after the other, tiles staged through registers): 4096 x 32 heads 148.7
+    // -> 137.9 us, 16384 x 64 heads 4069 -> 3827 us (1081 -> 1149 TFLOP/s).
     constexpr int kT = Swizzle<D>::kTile;
     const u32x4_t bk = buffer_words(K + kvoff), bv = buffer_words(V + kvoff);
     TileCopy<D, NW> cp;

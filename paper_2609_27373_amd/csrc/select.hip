@@ -139,9 +139,9 @@ __device__ int cut_by_rank(const float x[E], int cnt, double tau, uint64_t* lds,
 // (exponent at most 28 below the total's) the ordered prefix sums are plain
 // sums, and the cut is found digit by digit of the mass bits from sums per digit.  The light
 // masses only follow the heavy ones in the order; they matter for the total,
-// which the ordered sum rounds at each of up to 1024 of them: the true one is
-// within 2^-43 of a sum in any order, and a cut that is the same at both ends
-// of that range (here 2^-42) is the cut.  Returns false (nothing decided) for
+// which the ordered sum rounds at each of up to 1024 of them: it is within 1050
+// roundings (2^-53 each) of a sum in any order, and a cut that is the same at
+// both ends of that range (here 2^-42) is the cut.  Returns false (nothing decided) for
 // negative, infinite or NaN masses, a cut among the light ones, or one that
 // the range leaves open: cut_by_rank then does the row.  On success sel[e] tells
 // whether candidate lane + 64 e is among the first k*.
