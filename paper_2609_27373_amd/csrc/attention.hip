@@ -1153,16 +1153,19 @@ sparse_group_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
 // (batch, head, query block) row, a tile per block.  K and V are copied
 // straight into LDS, one tile each (12 KB at d 96): the next tile's K as soon
 // as this one's is in registers, its V after PV, so each has half a tile of
-// work to land, and no registers hold tiles in flight (124 VGPRs at d 96, 102
-// at d 64: LDS decides how many waves fit a CU).  The online softmax groups
-// keys in 32s, so a full support does not reproduce the dense kernel's bits.
+// work to land, and no registers hold tiles in flight.  LDS decides how many
+// waves fit a CU at d 96 (13) and 128 (10), registers at d 64 (102: 16 waves).
+// The online softmax groups keys in 32s, so a full support does not reproduce
+// the dense kernel's bits.
 //
-// Bound by the L2, which serves 10.4 GB at 4096 x 220 heads, d 96, density
-// 0.36, at 21 TB/s (25-32 for contiguous copies alone), and by what the SIMDs
-// leave of each other's waits.  Against tiles staged through registers (one
-// more tile of 48 VGPRs in flight, LDS written by the wave): 536 -> 496 us
-// there, 276 -> 259 us at 192 grouped heads of 64, 182 -> 153 us at 32 heads
-// of 128.
+// Every row reads its own K and V through L2: 80 million 128-byte requests (10.3
+// GB, 90% hits) at 4096 x 220 heads, d 96, density 0.40, 506 us or 20 TB/s; bound
+// by that and by the round trip, of which a wave hides half a tile's work.
+// Against tiles staged through registers (one more tile of 48 VGPRs in flight,
+// LDS written by the wave): 545 -> 506 us there, 305 -> 288 at 192 grouped heads
+// of 64 (45 million requests), 182 -> 153 at 32 heads of 128; rows of about five
+// blocks are slower (d 128, 4096 x 220 heads at density 0.05 230 -> 250 us): their
+// first tile, and what the round trip is longer than half a tile, weigh more.
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : D == 96 ? 3 : 2)))
@@ -1260,10 +1263,10 @@ sparse_row32_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
 // PV, so each has half a tile of work to land and 13 waves fit a CU.  A last
 // tile with one block takes it twice and masks the copy.
 //
-// Bound by the L2: every row reads its own K and V (12.7 GB at 4096 x 220
-// heads, d 96, density 0.23, 94% L2 hits) at 22 TB/s, where contiguous copies
-// from L2 alone reach 25-32.  843 -> 556 us there and 348 -> 262 us at 192
-// grouped heads of 64, against 32x32x16 MFMAs with the queries held twice and
+// Bound by the L2: every row reads its own K and V, 99 million 128-byte requests
+// (12.7 GB, 94% hits) at 4096 x 220 heads, d 96, density 0.28, 549 us or 23 TB/s.
+// 840 -> 549 us there and 348 -> 262 us at 192 grouped heads of 64, against
+// 32x32x16 MFMAs with the queries held twice and
 // tiles staged through registers; K read straight into registers (64-byte
 // pieces of rows, half the L2 rate) took 664 and 400 us.
 // ---------------------------------------------------------------------------
