@@ -220,10 +220,10 @@ wise_status wise_select_support_noalloc(const wise_shape* s, const float* acc,
  *               0..qb are skipped on the device (never read out of bounds);
  *               ordering and uniqueness are trusted, not re-checked.
  *   row_order : int32 [rows], a permutation of 0..rows-1, or NULL for the
- *               identity.  Schedule slot s runs row row_order[s]; slots are
- *               dealt to the 8 XCDs in contiguous ranges (slot s on XCD
- *               s / (rows / 8) when rows % 8 == 0), so rows of one head placed
- *               together share an L2.
+ *               identity.  Schedule slot s runs row row_order[s].  The slots of
+ *               a head (s / nb) run on as few of the 8 XCDs as even shares
+ *               allow, earlier ones first, so rows of one head placed together
+ *               share an L2.
  *   o         : bf16, same shape as q, written.  A row with an empty support
  *               writes zeros (and lse = -inf).
  *   lse       : fp32 [batch][heads][seq_len] or NULL.
